@@ -91,10 +91,15 @@ __host__ __device__ inline int64_t pair_index(int a, int b, int n) {
 }
 
 // Launchers (each returns hipError_t of the launch).
-hipError_t launch_sino_weight(const float *images, const double *intr, int n_views, int W, int H, float *gw,
-                              float *gwT, hipStream_t s);
-hipError_t launch_sino_radon(const float *gw, const float *gwT, const double *intr, int n_views, int W, int H,
-                             int n_alpha, int n_t, double ds, double *G, hipStream_t s);
+// line sums by image columns: gw, gwT ceil(n_views / 4) W H float4 each (scratch)
+bool radon_by_columns(int n_views, int W, int H, int n_t);
+hipError_t launch_sino_radon(const float *images, const double *intr, int n_views, int W, int H, int n_alpha, int n_t,
+                             double ds, float *gw, float *gwT, double *G, hipStream_t s);
+// line sums by gathered samples, from zeroed scratch
+hipError_t launch_sino_weight_pairs(const float *images, const double *intr, int n_views, int W, int H, float *gw,
+                                    float *gwT, hipStream_t s);
+hipError_t launch_sino_radon_gather(const float *gw, const float *gwT, const double *intr, int n_views, int W, int H,
+                                    int n_alpha, int n_t, double ds, double *G, hipStream_t s);
 hipError_t launch_sino_store(const double *G, const float *ext, int n_views, int n_alpha, int n_t, double dt,
                              int dtype, void *sino, float *view_scale, uint32_t *view_absmax, hipStream_t s);
 hipError_t launch_sino_read(const void *sino, const float *view_scale, SinoLayout L, int view, float *out,

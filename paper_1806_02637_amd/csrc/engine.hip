@@ -370,8 +370,12 @@ static ecc_status install_sinograms(ecc_ctx *ctx, Scan *s, int32_t n_alpha, int3
     uint64_t tmp_charged = 0;
     float *gw = nullptr, *gwT = nullptr, *ext_tmp = nullptr;
     double *G = nullptr;
-    // weighted projections in two orientations, rows stored as interleaved pairs
-    const uint64_t pad_bytes = 2 * sizeof(float) * (uint64_t)s->n_views * (s->W + 2 * kImgPad) * (s->H + 2 * kImgPad);
+    // weighted projections in two orientations: four views to an element, or (gathered samples)
+    // bordered with rows stored as interleaved pairs
+    const bool cols = radon_by_columns(s->n_views, s->W, s->H, n_t);
+    const uint64_t pad_bytes =
+        sizeof(float) * (cols ? (uint64_t)(s->n_views + 3) / 4 * 4 * s->W * s->H
+                              : 2ull * s->n_views * (s->W + 2 * kImgPad) * (s->H + 2 * kImgPad));
     const uint64_t G_bytes = sizeof(double) * (uint64_t)s->n_views * n_alpha * n_t;
     const uint64_t ext_bytes = sizeof(float) * (uint64_t)s->n_views * (n_alpha + 1) * n_t;
     auto cleanup = [&]() {
@@ -401,12 +405,15 @@ static ecc_status install_sinograms(ecc_ctx *ctx, Scan *s, int32_t n_alpha, int3
             (st = ctx_alloc(ctx, (void **)&gwT, pad_bytes, &tmp_charged)) ||
             (st = ctx_alloc(ctx, (void **)&G, G_bytes, &tmp_charged)))
             return bail(st);
-        if ((e = hipMemsetAsync(gw, 0, pad_bytes, stream)) != hipSuccess ||
-            (e = hipMemsetAsync(gwT, 0, pad_bytes, stream)) != hipSuccess ||
-            (e = launch_sino_weight(s->images_dev, s->intr_dev, s->n_views, s->W, s->H, gw, gwT, stream)) !=
-                hipSuccess ||
-            (e = launch_sino_radon(gw, gwT, s->intr_dev, s->n_views, s->W, s->H, n_alpha, n_t, ds_px, G, stream)) !=
-                hipSuccess)
+        if (cols)
+            e = launch_sino_radon(s->images_dev, s->intr_dev, s->n_views, s->W, s->H, n_alpha, n_t, ds_px, gw, gwT, G,
+                                  stream);
+        else if ((e = hipMemsetAsync(gw, 0, pad_bytes, stream)) == hipSuccess &&
+                 (e = hipMemsetAsync(gwT, 0, pad_bytes, stream)) == hipSuccess &&
+                 (e = launch_sino_weight_pairs(s->images_dev, s->intr_dev, s->n_views, s->W, s->H, gw, gwT, stream)) ==
+                     hipSuccess)
+            e = launch_sino_radon_gather(gw, gwT, s->intr_dev, s->n_views, s->W, s->H, n_alpha, n_t, ds_px, G, stream);
+        if (e != hipSuccess)
             return bail(fail(ECC_E_HIP, "sinogram build launch failed: %s", hipGetErrorString(e)));
     }
     const double t_max = 0.5 * sqrt((double)s->W * s->W + (double)s->H * s->H);

@@ -1,0 +1,168 @@
+// Line sums of a scan's weighted images by image columns (host and device code).
+//
+// The bilinear samples of a line at spacing ds are summed with tent weights:
+// sample j at (p_j, q_j) gives pixel (p, q) the weight T(p - p_j) T(q - q_j),
+// T(x) = max(0, 1 - |x|), p the axis the line runs along (|dq/dp| <= 1) and q
+// the other one.  So a line's sum is a weighted sum of pixels, and the weight
+// of a pixel,
+//   w = sum_j T(p - p_j) T(q - q_j),
+// depends on the angle, the line and the pixel but not on the view: all views
+// share the grid and the principal point (the detector centre).  A strip is 64
+// consecutive pixels of one column p, sheared along with the lines: lane i
+// holds pixel q = Q0 + i + floor(s (p - pc)), s = dq/dp the slope, so that a
+// line stays over the same lanes along the whole strip and a lane meets only
+// kLines consecutive lines.  Lines are numbered in ascending order of their
+// q at the middle column, kappa_k = kappa_0 + k dkappa.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+namespace ecc {
+
+#define ECC_RADON_HD __host__ __device__ __forceinline__
+
+constexpr int kStripLanes = 64;
+
+// One angle's lines (those with index r + R k of the full set of n_t) and the
+// strips that cover them.
+struct RadonAngle {
+    int P, Q;         // columns (along the lines), pixels per column
+    bool trans;       // p = image rows (y), q = image columns (x); else the other way round
+    bool flip;        // line k of the strips is line n_t - 1 - k of the sinogram
+    int n_lines;
+    double s;         // slope dq/dp
+    double h;         // signed p-step of a sample, ds dp
+    double inv_h;
+    double rho;       // a pixel can meet lines closer than rho = 1 + |s| along q
+    double kappa0, dkappa;
+    double pfirst, dpl;  // p at s = 0 of line k: pfirst + k dpl
+    int stride;          // lines of a strip: kappa in [origin + rho - 1, + stride)
+    double origin0;      // first lane of strip 0
+};
+
+// sa, ca: sine and cosine of the line angle; (cx, cy): the detector centre.
+ECC_RADON_HD RadonAngle radon_angle(double sa, double ca, int W, int H, int n_t, double t_max, double dt, double ds,
+                                    int r, int R) {
+    RadonAngle g;
+    const double cx = 0.5 * (W - 1), cy = 0.5 * (H - 1);
+    g.trans = fabs(sa) <= fabs(ca);
+    g.P = g.trans ? H : W;
+    g.Q = g.trans ? W : H;
+    const double dp = g.trans ? ca : -sa, dq = g.trans ? -sa : ca;
+    const double across = g.trans ? ca : sa;  // kappa = q centre + t / across
+    g.flip = across < 0.0;
+    g.s = dq / dp;
+    g.h = ds * dp;
+    g.inv_h = 1.0 / g.h;
+    g.rho = 1.0 + fabs(g.s);
+    g.n_lines = (n_t - r + R - 1) / R;
+    const double t0 = (g.flip ? t_max : -t_max) + (g.flip ? -r * dt : r * dt);
+    const double step = (g.flip ? -dt : dt) * R;
+    g.kappa0 = (g.trans ? cx : cy) + t0 / across;
+    g.dkappa = step / across;
+    const double along = g.trans ? sa : ca;  // p at s = 0: p centre + t along
+    g.pfirst = (g.trans ? cy : cx) + t0 * along;
+    g.dpl = step * along;
+    g.stride = (int)floor(kStripLanes - 2.0 * g.rho);
+    g.origin0 = floor(g.kappa0 - g.rho + 1.0);
+    return g;
+}
+
+// First line of strip j (the last line of strip j - 1 precedes it).
+ECC_RADON_HD int strip_first_line(const RadonAngle &g, int j) {
+    const double k = ceil((g.origin0 + (double)j * g.stride + g.rho - 1.0 - g.kappa0) / g.dkappa);
+    return k <= 0.0 ? 0 : (k >= (double)g.n_lines ? g.n_lines : (int)k);
+}
+
+// Columns in which strip j's lanes can lie on the image (a superset).
+ECC_RADON_HD void strip_columns(const RadonAngle &g, int j, int &p_lo, int &p_hi) {
+    const double Q0 = g.origin0 + (double)j * g.stride, pc = 0.5 * (g.P - 1);
+    // Q0 + 63 + s (p - pc) >= 0 and Q0 + s (p - pc) <= Q - 1, one pixel of slack
+    const double lo = -Q0 - kStripLanes, hi = g.Q - Q0;
+    double a, b;
+    if (fabs(g.s) * g.P < 0.5) {
+        const bool any = lo <= 1.0 && hi >= -1.0;
+        a = any ? 0.0 : 1.0;
+        b = any ? (double)g.P : 0.0;
+    } else {
+        const double x = lo / g.s + pc, y = hi / g.s + pc;
+        a = fmin(x, y) - 2.0;
+        b = fmax(x, y) + 3.0;
+    }
+    a = fmin(fmax(a, 0.0), (double)g.P);
+    b = fmin(fmax(b, 0.0), (double)g.P);
+    p_lo = (int)a;
+    p_hi = (int)b;
+    if (p_hi < p_lo) p_hi = p_lo;
+}
+
+// First of the consecutive lines that lane i of a strip at Q0 can meet.
+ECC_RADON_HD int lane_first_line(const RadonAngle &g, double Q0, int i) {
+    return (int)floor((Q0 + i - 1.0 - g.rho - g.kappa0) / g.dkappa) + 1;
+}
+
+// Lanes that line k can meet (inclusive).
+ECC_RADON_HD void line_lanes(const RadonAngle &g, double Q0, int k, int &i_lo, int &i_hi) {
+    const double x = g.kappa0 + k * g.dkappa - Q0;
+    i_lo = (int)floor(x - g.rho) + 1;
+    i_hi = (int)ceil(x + 1.0 + g.rho) - 1;
+    if (i_lo < 0) i_lo = 0;
+    if (i_hi > kStripLanes - 1) i_hi = kStripLanes - 1;
+}
+
+// Lines a lane can meet at most: the lines of an open kappa interval of
+// length 3 + 2 |s| spaced R dt sqrt(1 + s^2); (3 + 2 s) / sqrt(1 + s^2) is
+// largest at s = 2/3.
+inline int radon_lines_per_lane(double spacing) { return (int)ceil(3.6056 / spacing); }
+
+// Sample index (as a real number) at which line k passes column p.
+ECC_RADON_HD double sample_at(const RadonAngle &g, int k, double p, double c) {
+    return (p - (g.pfirst + k * g.dpl)) * g.inv_h + c;
+}
+
+// Columns at least this far from the middle may see samples beyond the line's
+// ends: |s| > t_max inside the tents around the image needs |p - pc| >
+// sqrt(t_max^2 - ((Q + 1) / 2)^2), less one column for the tent and one for
+// rounding.
+ECC_RADON_HD double radon_end_zone(int P, int Q) {
+    const double x = 0.25 * P * P - 0.5 * Q - 0.25;
+    return x > 0.0 ? sqrt(x) - 2.0 : -1.0;
+}
+
+ECC_RADON_HD float radon_tent(float x) { return fminf(fmaxf(1.0f - fabsf(x), 0.0f), 1.0f); }
+
+// 32-bit fraction of a real number.
+ECC_RADON_HD uint32_t fraction_bits(double x) {
+    return (uint32_t)(int64_t)floor((x - floor(x)) * 4294967296.0);
+}
+ECC_RADON_HD float fraction_value(uint32_t b) { return (float)b * 2.3283064365386963e-10f; }
+
+// A pixel's q-offset from a line (|x| < 8) in units of 2^-28 px: kept as an
+// integer until the column's fraction is taken off, since a rounding that
+// repeats along a line would not average out.
+ECC_RADON_HD int offset_bits(double x) { return (int)rint(x * 268435456.0); }
+ECC_RADON_HD float offset_value(int b) { return (float)b * 3.7252902984619140625e-9f; }
+
+// Weight of a pixel for a line: b = its q-offset from the line in its column,
+// phi = the fraction of the sample index at the column, samples at
+// phi + m, m = -M .. M - 1 (M >= 1 / |h|).  With ENDS only the samples
+// first + M - 1 - m ... inside [0, n_s) count, first = floor(index) + 1 - M.
+template <int M_FIXED, bool ENDS>
+ECC_RADON_HD float radon_weight(float b, float phi, float s, float h, int M_dyn, int index, int n_s) {
+    const int M = M_FIXED > 0 ? M_FIXED : M_dyn;
+    float w = 0.0f;
+    const float x0 = phi * h, y0 = fmaf(s, x0, b), hs = s * h;
+#pragma unroll
+    for (int m = -M; m < M; ++m) {
+        // p and q offsets of the pixel from sample j = index - m
+        const float x = fmaf((float)m, h, x0), y = fmaf((float)m, hs, y0);
+        float ww = radon_tent(x) * radon_tent(y);
+        if (ENDS) ww = (index - m >= 0 && index - m < n_s) ? ww : 0.0f;
+        w += ww;
+    }
+    return w;
+}
+
+}  // namespace ecc

@@ -1,0 +1,70 @@
+"""Sinogram builds on both sides of the rule that picks the column form of the
+line sums, at the sizes where it can go wrong: every number of lines per lane,
+interleaved line sets, sample steps, detectors smaller than a strip, view
+counts off the groups of four and eight, and non-finite pixels."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1806_02637_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def eng():
+    import torch
+
+    from paper_1806_02637_amd import engine
+
+    assert torch.cuda.is_available()
+    e = engine.Engine(0)
+    yield e
+    e.close()
+
+
+def _build(eng, images, W, H, n_alpha, n_t, ds):
+    g = inputs.ScanGeometry(len(images), W, H, 300.0 / W)
+    scan = eng.load_scan(g.projection_matrices(), g.intrinsics(), images)
+    scan.build_sinograms(n_alpha, n_t, ds, "f32")
+    out = np.stack([scan.read_sinogram(v) for v in range(len(images))])
+    scan.free()
+    return g, out
+
+
+@pytest.mark.parametrize("n_views,W,H,n_alpha,n_t,ds", [
+    (13, 70, 50, 24, 40, 0.5),    # 2 lines per lane
+    (17, 97, 61, 20, 75, 0.7),    # 3
+    (12, 64, 64, 20, 91, 1.0),    # 4
+    (33, 61, 130, 18, 200, 0.3),  # 5 to 6, many samples per column
+    (12, 48, 40, 16, 300, 0.5),   # interleaved sets of lines
+    (14, 2, 3, 8, 5, 1.0),        # a detector of a few pixels
+    (37, 300, 9, 16, 240, 0.5),   # a wide, low detector
+    (11, 64, 64, 20, 91, 0.5),    # too few views: gathered samples
+    (12, 64, 64, 20, 4, 0.5),     # lines 30 px apart: gathered samples
+])
+def test_build_matches_oracle(eng, n_views, W, H, n_alpha, n_t, ds):
+    print(f"case: build {n_views} views {W}x{H} -> {n_alpha}x{n_t} ds {ds}", flush=True)
+    images = np.random.default_rng(W + n_t).uniform(0.0, 50.0, (n_views, H, W)).astype(np.float32)
+    g, got = _build(eng, images, W, H, n_alpha, n_t, ds)
+    ref = oracle.FullSinograms.build(images, oracle.SinoGrid(W, H, n_alpha, n_t, ds), g.intrinsics()).data
+    for v in range(n_views):
+        # FP32 storage and partial sums, the bar of the other sinogram tests
+        assert np.abs(got[v] - ref[v]).max() <= 2e-5 * np.abs(ref[v]).max(), v
+
+
+def test_non_finite_pixels_reach_the_same_lines(eng):
+    """NaN and infinite pixels spoil the lines whose samples touch them and no
+    others, as in a build of fewer views (gathered samples)."""
+    print("case: build with non-finite pixels", flush=True)
+    images = np.random.default_rng(3).uniform(0.0, 50.0, (12, 60, 80)).astype(np.float32)
+    images[2, 20, 31] = np.nan
+    images[3, 0, 79] = np.inf
+    images[5, 59, 0] = -np.inf
+    _, cols = _build(eng, images, 80, 60, 24, 64, 0.5)
+    _, gather = _build(eng, images[:11], 80, 60, 24, 64, 0.5)
+    finite = np.isfinite(gather)
+    assert not finite.all() and finite.mean() > 0.5
+    assert np.array_equal(np.isfinite(cols[:11]), finite)
+    scale = np.abs(gather[finite]).max()
+    assert np.abs(cols[:11][finite] - gather[finite]).max() <= 2e-5 * scale

@@ -537,7 +537,7 @@ static ecc_status check_spline(ecc_ctx *ctx, int32_t B, int32_t n_views, int32_t
 namespace {
 
 struct FdkWorkspace {
-    uint64_t theta_off, nom_off, mov_off, views_off, pw_off, xw_off, q_off, total;
+    uint64_t theta_off, nom_off, mov_off, views_off, pw_off, parts_off, q_off, total;
 };
 
 FdkWorkspace fdk_workspace_layout(const Scan *s) {
@@ -553,7 +553,7 @@ FdkWorkspace fdk_workspace_layout(const Scan *s) {
     off += align256(sizeof(FdkView) * (uint64_t)s->n_views);
     w.pw_off = off;
     off += align256(sizeof(float) * (uint64_t)s->n_views * s->W);
-    w.xw_off = off;
+    w.parts_off = off;
     off += align256(sizeof(float) * (uint64_t)s->n_views * s->H * s->W);
     w.q_off = off;
     off += align256(sizeof(float) * 2ull * s->n_views * (s->H + 3) * (uint64_t)(s->W + 4));
@@ -642,7 +642,7 @@ ecc_status ecc_fdk(ecc_ctx *ctx, int32_t scan_id, const double *theta_dev, const
     const double depth = fabs(p0[11]) / sqrt(p0[8] * p0[8] + p0[9] * p0[9] + p0[10] * p0[10]);
     const float px_per_voxel = (float)(s->intr_host[0] * vol->voxel_mm / depth);
     HIP_TRY(launch_fdk(images_dev, nom, theta_dev ? mov : nom, s->n_views, s->W, s->H, fv,
-                       (FdkView *)(ws + w.views_off), (float *)(ws + w.pw_off), (float *)(ws + w.xw_off),
+                       (FdkView *)(ws + w.views_off), (float *)(ws + w.pw_off), (float *)(ws + w.parts_off),
                        (float *)(ws + w.q_off), px_per_voxel, (float)depth, out_dev, hs));
     return ECC_OK;
 }

@@ -7,12 +7,10 @@
 //                angular step, source distance D, and the moved P' in FP32.
 // fdk_parker     Parker's short-scan weight (Parker 1982) of every (view,
 //                column).
-// fdk_weight     cosine- and Parker-weighted detector rows, split by column
-//                parity.
-// fdk_filter_mfma  the sampled ramp filter (Kak and Slaney, ch. 3: h(0) = 1/4,
-//                h(n) = -1/(pi n)^2 for odd n) of every weighted detector
-//                row, as two Toeplitz matrix products
-//                on the matrix cores (one per output-column parity), scaled by
+// fdk_filter_split  cosine- and Parker-weighted detector rows through the
+//                sampled ramp filter (Kak and Slaney, ch. 3: h(0) = 1/4, h(n) =
+//                -1/(pi n)^2 for odd n), as two Toeplitz matrix products on
+//                the matrix cores (one per output-column parity), scaled by
 //                dbeta D^2 and written inside a two-wide zero border
 //                (fdk_border writes the border).
 // fdk_backproject  16 x 16 voxel columns x 16 slices per workgroup; each
@@ -90,21 +88,7 @@ __device__ __forceinline__ float parker(float beta, float gamma, float delta) {
 }
 
 // ---------------------------------------------------------------------------
-// The ramp filter as a matrix product on the matrix cores.  Split the outputs
-// by column parity p, u = 2i + p.  The filter's off-diagonal taps are odd,
-// so they pair each output with the inputs of the other parity,
-// k = 2j + 1 - p, and u - k = 2(i - j) + 2p - 1: per parity
-// Q_p = X_q G_p + X_p / 4 with the Toeplitz G_p[j][i] = h(2(i - j) + 2p - 1).
-// The rows of X are all detector rows of all views, so each parity is one
-// (N H) x (W / 2) x (W / 2) FP32 product (v_mfma_f32_32x32x2f32), half the
-// multiply-adds of the plain convolution.  A (weighted inputs) is staged in
-// LDS per 32-input step; B is read from the 1-D table of G_p's diagonals.
-
 typedef float fdk_v16f __attribute__((ext_vector_type(16)));
-
-constexpr int kMmRows = 64;   // detector rows per workgroup (2 waves of 32)
-constexpr int kMmCols = 128;  // outputs of one parity per workgroup (2 waves of 2 x 32)
-constexpr int kMmK = 32;      // inputs staged per step
 
 // Parker weight of every (view, column).
 __global__ __launch_bounds__(256) void fdk_parker_kernel(const FdkView *__restrict__ views, int n_views, int W,
@@ -116,113 +100,229 @@ __global__ __launch_bounds__(256) void fdk_parker_kernel(const FdkView *__restri
     pw[idx] = parker(vw.beta, -atanf(du / vw.f), vw.delta);
 }
 
-// Weighted inputs x(r, k) = p(r, k) * cosine weight * Parker weight, split by
-// column parity: X_even[r][j] = x(r, 2j) ([N H][ceil(W / 2)]) and
-// X_odd[r][j] = x(r, 2j + 1) ([N H][floor(W / 2)]), so the products read
-// contiguous rows.
-__global__ __launch_bounds__(256) void fdk_weight_kernel(const float *__restrict__ images,
-                                                         const FdkView *__restrict__ views,
-                                                         const float *__restrict__ pw, int W, int H,
-                                                         float *__restrict__ x_even, float *__restrict__ x_odd) {
-    const int k = blockIdx.y * blockDim.x + threadIdx.x;
-    const int64_t r = blockIdx.x;  // view * H + v
-    if (k >= W) return;
-    const int view = (int)(r / H), v = (int)(r % H);
-    const FdkView vw = views[view];
-    const float du = (float)k - vw.u0, dv = (float)v - vw.v0;
-    const float cosw = vw.f * rsqrtf(vw.f * vw.f + du * du + dv * dv);
-    const float x = images[r * W + k] * cosw * pw[(int64_t)view * W + k];
-    if (k & 1) x_odd[r * (W / 2) + (k >> 1)] = x;
-    else x_even[r * ((W + 1) / 2) + (k >> 1)] = x;
+// The ramp filter as a matrix product on the matrix cores.  The weighted inputs
+// are x(r, k) = p(r, k) * cosine weight * Parker weight.  Split the outputs by
+// column parity p, u = 2i + p.  The filter's off-diagonal taps are odd, so
+// they pair each output with the inputs of the other parity, k = 2j + 1 - p,
+// and u - k = 2(i - j) + 2p - 1: per parity Q_p = X_q G_p + X_p / 4 with the
+// Toeplitz G_p[j][i] = h(2(i - j) + 2p - 1).  The rows of X are all detector
+// rows of all views, so each parity is one (N H) x (W / 2) x (W / 2) product,
+// half the multiply-adds of the plain convolution.
+//
+// It runs on the bf16 matrix cores, in FP32: every factor is split
+// into three bf16 pieces that add up to it exactly (8 + 8 + 8 bits), and the
+// six products of pieces down to 2^-16 of the largest are accumulated in FP32
+// (v_mfma_f32_32x32x16_bf16); the three left out are below 2^-24 of the
+// product, its rounding in FP32.  The weights are applied on the way in.
+//
+// A workgroup = 64 detector rows x 128 NT outputs of one parity, 8 waves of 32
+// rows x NT blocks of 32 outputs.  Inputs are weighted, split and staged 32 at
+// a time (double-buffered).  Block (i, j) of the Toeplitz matrix depends on
+// i - j only: its pieces come from a table of the diagonals in LDS, held in 8
+// copies shifted by one element each, so that any lane's 8 consecutive
+// elements are one aligned 16-byte read.
+//
+// 496 views of 1240 x 960: 4.3 ms; 9.4 ms with a weighting pass (1.85) and
+// FP32 matrix instructions (7.55).  The six products take 1.9 ms at the matrix
+// cores' rate, 47 % of the cycles (2.1 GHz under this load); the rest is the
+// weights, splits and sums of the two waves of a SIMD, which meet at every
+// step's barrier.  248 views of 620 x 480: 0.48 against 0.93 ms.  Against a
+// 64-bit filter the rows are 1.3e-5 off (1240 columns; 3.1e-5 before).
+typedef __bf16 fdk_bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 fdk_bf16x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kFltRows = 64;
+constexpr int kFltK = 32;
+constexpr int kFltPitch = kFltK + 8;  // 80-byte rows: conflict-free 16-byte reads
+
+// Elements of the diagonals' table for `cols` outputs and `inputs` inputs, and
+// the bytes one shifted copy takes (16 past a multiple of 128: consecutive
+// lanes read consecutive copies).
+__host__ __device__ inline int flt_chunks(int cols, int inputs) { return ((cols + inputs + 15) / 8 + 7) / 8 * 8; }
+__host__ __device__ inline int flt_copy_bytes(int cols, int inputs) { return 16 * flt_chunks(cols, inputs) + 16; }
+inline size_t flt_table_bytes(int cols, int inputs) { return (size_t)24 * flt_copy_bytes(cols, inputs); }
+
+__device__ __forceinline__ void bf16_split(float x, __bf16 &h, __bf16 &m, __bf16 &l) {
+    h = (__bf16)x;
+    const float r = x - (float)h;
+    m = (__bf16)r;
+    l = (__bf16)(r - (float)m);
 }
 
-// Workgroups: (parity, row tile, column tile), numbered with the column tile
-// fastest and dealt so that each XCD takes a contiguous range: the column
-// tiles of one row tile share its inputs in the XCD's L2.  Dynamic LDS: the
-// diagonals of G_p, W - 1 floats.
-__global__ __launch_bounds__(256) void fdk_filter_mfma_kernel(const float *__restrict__ x_even,
-                                                              const float *__restrict__ x_odd,
-                                                              const FdkView *__restrict__ views, int n_views, int W,
-                                                              int H, int row_tiles, int col_tiles,
-                                                              float *__restrict__ Qp) {
-    __shared__ float As[kMmRows][kMmK + 1];
-    extern __shared__ float gs[];
+// Constants of one detector row's weights.
+struct FltRow {
+    float f, u0, dv, out_scale;  // focal length, principal column, v - v0, output scale
+    int64_t image, pw, out;      // offsets of the row in the images, its Parker weights and the filtered views
+};
+
+template <int NT>
+__global__ __launch_bounds__(512) void fdk_filter_split_kernel(const float *__restrict__ images,
+                                                               const float *__restrict__ pw,
+                                                               const FdkView *__restrict__ views, int n_views, int W,
+                                                               int H, int row_tiles, int col_tiles,
+                                                               float *__restrict__ Qp) {
+    constexpr int kCols = 128 * NT;
+    __shared__ __align__(16) __bf16 As[2][3][kFltRows][kFltPitch];
+    __shared__ FltRow rows[kFltRows];
+    extern __shared__ __align__(16) char table[];
+    // the two parities of a row tile are neighbours on an XCD: they read and
+    // write the same cache lines
     const int total = 2 * row_tiles * col_tiles;
     const int per = (total + 7) / 8;
     const int t = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
     if (t >= total) return;  // before any barrier
-    const int p = t / (row_tiles * col_tiles), rem = t % (row_tiles * col_tiles);
-    const int row_tile = rem / col_tiles, col_tile = rem % col_tiles;
+    const int p = t % 2, col_tile = t / 2 % col_tiles, row_tile = t / 2 / col_tiles;
     const int q = 1 - p;
     const int Wp = (W + 1 - p) / 2, Wq = (W + 1 - q) / 2;  // outputs of parity p, inputs of parity q
+    const int Kp = (Wq + kFltK - 1) / kFltK * kFltK;
     const int64_t n_rows = (int64_t)n_views * H;
-    const float *xq = q ? x_odd : x_even;  // [n_rows][Wq]
-    const float *xp = p ? x_odd : x_even;  // [n_rows][Wp]
-    // g[d + Wq - 1] = h(2d + 2p - 1), d = i - j in [-(Wq - 1), Wp - 1]
-    for (int e = threadIdx.x; e < Wp + Wq - 1; e += blockDim.x) {
-        const float n = (float)(2 * (e - (Wq - 1)) + 2 * p - 1);
-        gs[e] = -1.0f / (kPiF * kPiF * n * n);
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wr = wave >> 1, wc = wave & 1;
-    const int64_t r_base = (int64_t)row_tile * kMmRows;
-    const int i_base = col_tile * kMmCols + 64 * wc;
-    fdk_v16f acc0 = {0}, acc1 = {0};
-    // each thread stages 8 inputs of a step; the next step's are loaded into
-    // registers while this step's products run
-    constexpr int kPer = kMmRows * kMmK / 256;
-    float pre[kPer];
-    auto load_step = [&](int j0) {
-#pragma unroll
-        for (int e8 = 0; e8 < kPer; ++e8) {
-            const int e = threadIdx.x + 256 * e8;
-            const int64_t r = r_base + e / kMmK;
-            const int j = j0 + e % kMmK;
-            pre[e8] = (r < n_rows && j < Wq) ? xq[r * Wq + j] : 0.0f;
-        }
-    };
-    load_step(0);
-    for (int j0 = 0; j0 < Wq; j0 += kMmK) {
-        __syncthreads();  // the previous step's reads of As are done (and gs is written)
-#pragma unroll
-        for (int e8 = 0; e8 < kPer; ++e8) {
-            const int e = threadIdx.x + 256 * e8;
-            As[e / kMmK][e % kMmK] = pre[e8];
-        }
-        __syncthreads();
-        if (j0 + kMmK < Wq) load_step(j0 + kMmK);
-#pragma unroll 4
-        for (int kk = 0; kk < kMmK; kk += 2) {
-            const float a = As[32 * wr + (lane & 31)][kk + (lane >> 5)];
-            const int j = j0 + kk + (lane >> 5);
-            const int i0 = i_base + (lane & 31), i1 = i0 + 32;
-            const bool jok = j < Wq;
-            const float b0 = (jok && i0 < Wp) ? gs[i0 - j + Wq - 1] : 0.0f;
-            const float b1 = (jok && i1 < Wp) ? gs[i1 - j + Wq - 1] : 0.0f;
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b0, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b1, acc1, 0, 0, 0);
-        }
-    }
-    // outputs: register e of lane l holds row 8 (e / 4) + 4 (l / 32) + e % 4,
-    // column l % 32 of the wave's 32 x 32 block
-    const int WP = W + 4;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int64_t r = r_base + 32 * wr + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4);
-        if (r >= n_rows) continue;
+    const int64_t r_base = (int64_t)row_tile * kFltRows;
+    const int i_tile = col_tile * kCols;
+    const int copy = flt_copy_bytes(kCols, Kp);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid < kFltRows) {
+        // rows past the last repeat it (their outputs are not written)
+        const int64_t r = min(r_base + tid, n_rows - 1);
         const int view = (int)(r / H), v = (int)(r % H);
         const FdkView &vw = views[view];
-        const float out_scale = vw.inv_tau * vw.scale;
-        float *row = Qp + ((int64_t)view * (H + 4) + (v + 2)) * WP;
+        rows[tid] = FltRow{vw.f,  vw.u0, (float)v - vw.v0,  vw.inv_tau * vw.scale,
+                           r * W, (int64_t)view * W, ((int64_t)view * (H + 4) + v + 2) * (W + 4) + 2};
+    }
+    // element e of the table: the tap of i - j = i_tile + kCols - 1 - e
+    for (int e = tid; e < kCols + Kp + 8; e += 512) {
+        const float n = (float)(2 * (i_tile + kCols - 1 - e) + 2 * p - 1);
+        __bf16 piece[3];
+        bf16_split(-1.0f / (kPiF * kPiF * n * n), piece[0], piece[1], piece[2]);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int i = (h == 0 ? i_base : i_base + 32) + (lane & 31);
-            if (i >= Wp) continue;
-            const int u = 2 * i + p;
-            const float acc = h == 0 ? acc0[e] : acc1[e];
-            row[u + 2] = fmaf(0.25f, xp[r * Wp + i], acc) * out_scale;
+        for (int c = 0; c < 8; ++c) {
+            const int x = e - c;  // copy c holds element x + c at x
+            if (x < 0 || x >= 8 * flt_chunks(kCols, Kp)) continue;
+#pragma unroll
+            for (int z = 0; z < 3; ++z) *(__bf16 *)(table + (8 * z + c) * copy + 2 * x) = piece[z];
         }
     }
+    __syncthreads();
+    auto cosine = [](const FltRow &row, int k) {
+        const float du = (float)k - row.u0;
+        return row.f * __builtin_amdgcn_rsqf(row.f * row.f + du * du + row.dv * row.dv);
+    };
+    // staging: thread -> row tid / 8, inputs 4 (tid % 8) .. + 3 of the step
+    const int s_row = tid >> 3, s_j = 4 * (tid & 7);
+    const FltRow mine = rows[s_row];
+    float pre[4], pre_w[4];
+    auto load_step = [&](int j0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int k = 2 * min(j0 + s_j + c, Wq - 1) + q;
+            pre[c] = images[mine.image + k];
+            pre_w[c] = pw[mine.pw + k];
+        }
+    };
+    auto store_step = [&](int j0, int buf) {
+        fdk_bf16x4 v[3];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int j = j0 + s_j + c;
+            const float x = pre[c] * cosine(mine, 2 * j + q) * pre_w[c];
+            __bf16 h, m, l;
+            bf16_split(j < Wq ? x : 0.0f, h, m, l);
+            v[0][c] = h, v[1][c] = m, v[2][c] = l;
+        }
+#pragma unroll
+        for (int z = 0; z < 3; ++z) *(fdk_bf16x4 *)&As[buf][z][s_row][s_j] = v[z];
+    };
+    const int wr = wave & 1, wc = wave >> 1;
+    // this lane's first table element for its first block at input 0
+    const int first = kCols - 1 - (wc * NT * 32 + (lane & 31)) + 8 * (lane >> 5);
+    const char *tab = table + (first & 7) * copy + (first >> 3) * 16;
+    // a step's products are accumulated from zero, then added to the total:
+    // only the steps around an output's own column round at the size of its
+    // sum, which nearly cancels against x_p / 4
+    fdk_v16f acc[NT], tot[NT];
+#pragma unroll
+    for (int b = 0; b < NT; ++b) tot[b] = fdk_v16f{0};
+    load_step(0);
+    store_step(0, 0);
+    int buf = 0;
+    for (int j0 = 0; j0 < Kp; j0 += kFltK, buf ^= 1) {
+        const bool more = j0 + kFltK < Kp;
+        if (more) load_step(j0 + kFltK);
+        __syncthreads();  // this step's inputs are written; the other buffer's reads are done
+        // block n = 0 .. 2 NT - 1 of the step: outputs n % NT, inputs 16 (n / NT);
+        // the next block's pieces are read ahead of this one's products
+        fdk_bf16x8 a[2][3], g[2][3];
+        auto read_a = [&](int half) {
+#pragma unroll
+            for (int z = 0; z < 3; ++z)
+                a[half][z] = *(const fdk_bf16x8 *)&As[buf][z][32 * wr + (lane & 31)][16 * half + 8 * (lane >> 5)];
+        };
+        auto read_g = [&](int n) {
+            // 16 inputs on move a block two chunks up the table, 32 outputs
+            // four chunks down
+            const char *src = tab + (j0 / 8 + 2 * (n / NT) - 4 * (n % NT)) * 16;
+#pragma unroll
+            for (int z = 0; z < 3; ++z) g[n & 1][z] = *(const fdk_bf16x8 *)(src + 8 * z * copy);
+        };
+        read_a(0);
+        read_g(0);
+#pragma unroll
+        for (int n = 0; n < 2 * NT; ++n) {
+            if (n + 1 < 2 * NT) read_g(n + 1);
+            if (n == NT - 1) read_a(1);
+            __builtin_amdgcn_sched_barrier(0);
+            const int b = n % NT;
+            const fdk_bf16x8 *x = a[n / NT], *y = g[n & 1];
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[2], n < NT ? fdk_v16f{0} : acc[b], 0, 0, 0);
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2], y[0], acc[b], 0, 0, 0);
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[1], acc[b], 0, 0, 0);
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[1], acc[b], 0, 0, 0);
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[0], acc[b], 0, 0, 0);
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[0], acc[b], 0, 0, 0);
+            // the totals of blocks that are done, between the products
+            if (n > NT) tot[(n - 1) % NT] += acc[(n - 1) % NT];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        tot[NT - 1] += acc[NT - 1];
+        if (more) store_step(j0 + kFltK, buf ^ 1);
+    }
+    // outputs: register e of lane l holds row 8 (e / 4) + 4 (l / 32) + e % 4,
+    // column l % 32 of the wave's 32 x 32 block; four rows' x_p are read at a
+    // time (clamped to the detector) before their outputs are written
+#pragma unroll
+    for (int e0 = 0; e0 < 16; e0 += 4) {
+        float x[4][NT];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const FltRow &o = rows[32 * wr + 2 * e0 + 4 * (lane >> 5) + e];
+#pragma unroll
+            for (int b = 0; b < NT; ++b) {
+                const int k = 2 * min(i_tile + (wc * NT + b) * 32 + (lane & 31), Wp - 1) + p;
+                x[e][b] = images[o.image + k] * cosine(o, k) * pw[o.pw + k];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int row = 32 * wr + 2 * e0 + 4 * (lane >> 5) + e;
+            const FltRow &o = rows[row];
+            const bool on = r_base + row < n_rows;
+#pragma unroll
+            for (int b = 0; b < NT; ++b) {
+                const int i = i_tile + (wc * NT + b) * 32 + (lane & 31);
+                if (on && i < Wp) Qp[o.out + 2 * i + p] = fmaf(0.25f, x[e][b], tot[b][e0 + e]) * o.out_scale;
+            }
+        }
+    }
+}
+
+template <int NT>
+static hipError_t launch_filter_split(const float *images, const float *pw, const FdkView *views, int n_views, int W,
+                                      int H, int col_tiles, float *Qp, hipStream_t s) {
+    const int row_tiles = (int)(((int64_t)n_views * H + kFltRows - 1) / kFltRows);
+    const int total = 2 * row_tiles * col_tiles;
+    const int Kp = ((W + 1) / 2 + kFltK - 1) / kFltK * kFltK;
+    hipLaunchKernelGGL(fdk_filter_split_kernel<NT>, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(512),
+                       flt_table_bytes(128 * NT, Kp), s, images, pw, views, n_views, W, H, row_tiles, col_tiles, Qp);
+    return hipGetLastError();
 }
 
 // The zero border of the filtered views: rows 0, 1, H + 2, H + 3 and columns
@@ -529,7 +629,7 @@ static hipError_t launch_backproject(const float *Qp, const FdkView *views, int 
 }
 
 hipError_t launch_fdk(const float *images, const ViewGeom *nominal, const ViewGeom *moved, int n_views, int W,
-                      int H, FdkVolume vol, FdkView *views, float *pw, float *xw, float *Qp, float px_per_voxel,
+                      int H, FdkVolume vol, FdkView *views, float *pw, float *parts, float *Qp, float px_per_voxel,
                       float source_mm, float *out, hipStream_t s) {
     hipLaunchKernelGGL(fdk_view_kernel, dim3((n_views + 255) / 256), dim3(256), 0, s, nominal, moved, n_views,
                        views);
@@ -543,19 +643,13 @@ hipError_t launch_fdk(const float *images, const ViewGeom *nominal, const ViewGe
     hipLaunchKernelGGL(fdk_border_kernel, dim3((unsigned)((n_border + 255) / 256)), dim3(256), 0, s, n_views, W, H,
                        Qp);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    float *x_even = xw, *x_odd = xw + (int64_t)n_views * H * ((W + 1) / 2);
-    hipLaunchKernelGGL(fdk_weight_kernel, dim3((unsigned)((int64_t)n_views * H), (W + 255) / 256), dim3(256), 0, s,
-                       images,
-                       (const FdkView *)views, (const float *)pw, W, H, x_even, x_odd);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int row_tiles = (int)(((int64_t)n_views * H + kMmRows - 1) / kMmRows);
-    const int col_tiles = ((W + 1) / 2 + kMmCols - 1) / kMmCols;
-    const int total = 2 * row_tiles * col_tiles;
-    hipLaunchKernelGGL(fdk_filter_mfma_kernel, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(256),
-                       sizeof(float) * W, s, (const float *)x_even, (const float *)x_odd, (const FdkView *)views,
-                       n_views, W, H, row_tiles, col_tiles, Qp);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // the weighted rows are read: their scratch takes the parts of the views
+    const int half = (W + 1) / 2, col_tiles = (half + 639) / 640, nt = ((half + col_tiles - 1) / col_tiles + 127) / 128;
+    if (nt == 1) e = launch_filter_split<1>(images, pw, views, n_views, W, H, col_tiles, Qp, s);
+    else if (nt == 2) e = launch_filter_split<2>(images, pw, views, n_views, W, H, col_tiles, Qp, s);
+    else if (nt == 3) e = launch_filter_split<3>(images, pw, views, n_views, W, H, col_tiles, Qp, s);
+    else if (nt == 4) e = launch_filter_split<4>(images, pw, views, n_views, W, H, col_tiles, Qp, s);
+    else e = launch_filter_split<5>(images, pw, views, n_views, W, H, col_tiles, Qp, s);
+    if (e != hipSuccess) return e;
     const int64_t parts_floats = (int64_t)n_views * H * W;
     // rows of a tile's window: its 15 voxel steps at the magnification nearest
     // the source, a cell of margin on each side and the rounding to cells
@@ -563,8 +657,8 @@ hipError_t launch_fdk(const float *images, const ViewGeom *nominal, const ViewGe
     const float rows = r < source_mm ? px_per_voxel * 15.0f * source_mm / (source_mm - r) + 4.0f : 1e9f;
     // (512^3 at 0.4 mm fits 44 rows: 31.2 ms, 32.3 with 56)
     if (rows <= 44.0f)
-        return launch_backproject<44>(Qp, views, n_views, W, H, vol, xw, parts_floats, out, s);
-    return launch_backproject<56>(Qp, views, n_views, W, H, vol, xw, parts_floats, out, s);
+        return launch_backproject<44>(Qp, views, n_views, W, H, vol, parts, parts_floats, out, s);
+    return launch_backproject<56>(Qp, views, n_views, W, H, vol, parts, parts_floats, out, s);
 }
 
 }  // namespace ecc

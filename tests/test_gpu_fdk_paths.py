@@ -52,3 +52,34 @@ def test_fdk_paths(eng, n_views, W, H, pitch, vol, moved):
     peak = np.abs(ref).max()
     err = np.abs(got - ref)
     assert err.max() <= 1e-4 * peak and np.sqrt(np.mean(err ** 2)) <= 1e-5 * peak
+
+
+@pytest.mark.parametrize("n_views,W,H", [
+    (20, 255, 7),   # 2 blocks of outputs per wave, odd width, rows past the last tile
+    (20, 514, 5),   # 3
+    (20, 801, 4),   # 4
+    (20, 1278, 4),  # 5
+    (20, 1283, 3),  # two column tiles
+    (16, 4096, 2),  # the widest detector (the largest table of taps)
+])
+def test_fdk_filter_widths(eng, n_views, W, H):
+    """The ramp filter over its column tilings.  Q = x / 4 + off-diagonal sum
+    nearly cancels on wide smooth rows, so its FP32 error is a rounding of the
+    two terms, up to 2^-23 x_max / 4 each, scaled by f / D; the back-projection
+    adds it over the arc with weights near 1.  Bar: that, twice, plus the
+    position bar of 1e-4 of the peak."""
+    import torch
+
+    print(f"case: fdk filter {n_views} views {W}x{H}", flush=True)
+    g = inputs.ScanGeometry(n_views, W, H, 380.0 / W)
+    P, intr, betas, arc = g.projection_matrices(), g.intrinsics(), g.orbit_angles(), math.radians(g.arc_deg)
+    imgs = inputs.project(g, inputs.random_phantom(6, 6))
+    vol = (20, 18, 2, 0.6 * g.pitch_mm)
+    scan = eng.load_scan(P, intr, imgs)
+    got = scan.fdk(torch.tensor(imgs, device="cuda"), vol).cpu().numpy()
+    ref = ofdk.fdk(imgs, P, intr, betas, arc, g.sid_mm, ofdk.Volume(*vol))
+    scan.free()
+    bar = 1e-4 * np.abs(ref).max() + 2.0 * arc * (2.0 ** -23 * imgs.max() / 2.0) * g.f_px / g.sid_mm
+    err = np.abs(got - ref).max()
+    print(f"  max err {err:.2e} of peak {np.abs(ref).max():.3g}, bar {bar:.2e}", flush=True)
+    assert err <= bar

@@ -23,7 +23,8 @@
 //               detector arc's end moves as the zero angle of the corner that
 //               fixes it, atan2(-A_c, B_c) with (A_c, B_c) the two basis
 //               lines' values at the corner.
-// reduce_grad   fixed-order sum of the per-pair 12-vectors into grad[B][N][6].
+// reduce        fixed-order sums: the cost, and the per-pair 12-vectors into
+//               grad[B][N][6].
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(256) void ecc_adj_kernel(const void *__restrict__ s
 }
 
 // One thread per (hypothesis, pair): pair_gradient (pair_adjoint.hpp).
-__global__ __launch_bounds__(256) void pair_grad_kernel(const ViewGeom *__restrict__ vt,
+__global__ __launch_bounds__(64) void pair_grad_kernel(const ViewGeom *__restrict__ vt,
                                                         const ViewGeomGrad *__restrict__ vg,
                                                         const float *__restrict__ sens, EvalConsts ec,
                                                         float *__restrict__ pair_grad) {
@@ -293,19 +294,26 @@ hipError_t launch_ecc_adj(const void *sino, const void *table, const ViewGeom *v
     }
     if (e != hipSuccess) return e;
     const int64_t n = (int64_t)ec.B * ec.n_pairs;
-    hipLaunchKernelGGL(pair_grad_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, vt, vg, sens, ec,
+    hipLaunchKernelGGL(pair_grad_kernel, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s, vt, vg, sens, ec,
                        pair_grad);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
+// The first B workgroups sum the cost (reduce_cost); the others
 // grad[b][v][0..5] = sum over partners u of the pair (min, max)'s 12-vector:
 // entries 0..5 when v is the first view of the pair, 6..11 else.  One wave
 // per (hypothesis, view): lane l adds the partners u = l, l + 64, ... in
 // FP64, then the 64 lane sums are added in a fixed butterfly order.
-__global__ __launch_bounds__(256) void reduce_grad_kernel(const float *__restrict__ pair_grad, int B, int n_views,
-                                                          float *__restrict__ grad) {
-    const int64_t wid = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+__global__ __launch_bounds__(kReduceThreads) void reduce_kernel(const double *__restrict__ partials, int n_tiles,
+                                                                const float *__restrict__ pair_grad, int B, int n_views,
+                                                                double *__restrict__ out_cost,
+                                                                float *__restrict__ grad) {
+    if ((int)blockIdx.x < B) {
+        reduce_cost<kReduceThreads>(partials + (int64_t)blockIdx.x * n_tiles, n_tiles, out_cost + blockIdx.x);
+        return;
+    }
+    const int64_t wid = (int64_t)(blockIdx.x - B) * (kReduceThreads / 64) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (wid >= (int64_t)B * n_views) return;  // whole waves; no barriers
     const int b = (int)(wid / n_views), v = (int)(wid % n_views);
@@ -323,10 +331,11 @@ __global__ __launch_bounds__(256) void reduce_grad_kernel(const float *__restric
         for (int q = 0; q < 6; ++q) grad[wid * 6 + q] = (float)acc[q];
 }
 
-hipError_t launch_reduce_grad(const float *pair_grad, int B, int n_views, float *grad, hipStream_t s) {
-    const int64_t waves = (int64_t)B * n_views;
-    hipLaunchKernelGGL(reduce_grad_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, pair_grad, B, n_views,
-                       grad);
+hipError_t launch_reduce(const double *partials, int n_tiles, const float *pair_grad, int B, int n_views,
+                         double *out_cost, float *grad, hipStream_t s) {
+    const int64_t waves = (int64_t)B * n_views, per = kReduceThreads / 64;
+    hipLaunchKernelGGL(reduce_kernel, dim3((unsigned)(B + (waves + per - 1) / per)), dim3(kReduceThreads), 0, s, partials,
+                       n_tiles, pair_grad, B, n_views, out_cost, grad);
     return hipGetLastError();
 }
 

@@ -1,7 +1,8 @@
 // Epipolar-consistency cost on gfx950 (arxiv 1806.02637, Eqs. 13-17).
 //
 // view_setup   one thread per (hypothesis, view): P' = P T(theta) and its
-//              source (Eqs. 4-5), FP64; optionally dP'/dtheta for the adjoint.
+//              source (Eqs. 4-5), FP64; optionally dP'/dtheta for the adjoint
+//              (six threads).
 // pair_setup   one thread per (hypothesis, pair): the pair's geometry in FP64
 //              (baseline, pencil of planes, the two line maps of Eq. 14) ->
 //              a table of per-plane constants.
@@ -11,7 +12,9 @@
 //              (alpha, t) -> four bilinear taps per view in one load ->
 //              (S_a - S_b)^2 -> wave-shuffle sum (Eq. 15) -> Cauchy norm
 //              (Eq. 16).  No atomics; per-tile FP64 partials.
-// reduce_cost  fixed-order sum of the tile partials per hypothesis (Eq. 17).
+// reduce_cost  fixed-order sum of the tile partials per hypothesis (Eq. 17), in
+//              a launch of its own or, with few tiles, by the hypothesis's last
+//              workgroup of ecc_fwd.
 //
 // Blocks are numbered so that each of the 8 XCDs (which receive workgroups
 // round-robin) walks a contiguous run of tiles with the hypotheses of a tile
@@ -33,24 +36,28 @@ __device__ __forceinline__ void mat3_mul(const double A[9], const double B[9], d
         for (int j = 0; j < 3; ++j) C[3 * i + j] = A[3 * i] * B[j] + A[3 * i + 1] * B[3 + j] + A[3 * i + 2] * B[6 + j];
 }
 
-__global__ __launch_bounds__(256) void view_setup_kernel(const double *__restrict__ P, const double *__restrict__ intr,
-                                                         const double *__restrict__ theta, int B, int n_views,
-                                                         ViewGeom *__restrict__ vt, ViewGeomGrad *__restrict__ vg) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= B * n_views) return;
-    const int v = idx % n_views;
-    const double *th = theta + (int64_t)idx * 6;
+// A view's rotation: cosines and sines of its three angles, and Ry, Rz, Ry Rx.
+struct ViewRotation {
+    double c[3], s[3], Ry[9], Rz[9], RyRx[9];
+};
+
+// P' = P T(theta) and its source.
+__device__ __forceinline__ ViewGeom view_geometry(const double *Pv, const double *th, const double *intr,
+                                                  ViewRotation &r) {
     const double deg = 3.14159265358979323846 / 180.0;
-    double c[3], s[3];
-    for (int i = 0; i < 3; ++i) sincos(th[i] * deg, &s[i], &c[i]);
-    // R = Rz Ry Rx and the three partial derivatives
+    for (int i = 0; i < 3; ++i) sincos(th[i] * deg, &r.s[i], &r.c[i]);
+    const double *c = r.c, *s = r.s;
+    // R = Rz Ry Rx
     const double Rx[9] = {1, 0, 0, 0, c[0], -s[0], 0, s[0], c[0]};
     const double Ry[9] = {c[1], 0, s[1], 0, 1, 0, -s[1], 0, c[1]};
     const double Rz[9] = {c[2], -s[2], 0, s[2], c[2], 0, 0, 0, 1};
-    double RyRx[9], R[9];
-    mat3_mul(Ry, Rx, RyRx);
-    mat3_mul(Rz, RyRx, R);
-    const double *Pv = P + (int64_t)v * 12;
+    double R[9];
+    mat3_mul(Ry, Rx, r.RyRx);
+    mat3_mul(Rz, r.RyRx, R);
+    for (int i = 0; i < 9; ++i) {
+        r.Ry[i] = Ry[i];
+        r.Rz[i] = Rz[i];
+    }
     ViewGeom g;
     for (int i = 0; i < 3; ++i) {
         for (int j = 0; j < 3; ++j)
@@ -58,42 +65,69 @@ __global__ __launch_bounds__(256) void view_setup_kernel(const double *__restric
         g.P[4 * i + 3] = Pv[4 * i] * th[3] + Pv[4 * i + 1] * th[4] + Pv[4 * i + 2] * th[5] + Pv[4 * i + 3];
     }
     source_position(g.P, g.C);
-    g.f = intr[3 * v];
-    g.u0 = intr[3 * v + 1];
-    g.v0 = intr[3 * v + 2];
+    g.f = intr[0];
+    g.u0 = intr[1];
+    g.v0 = intr[2];
     g.pad[0] = g.pad[1] = 0.0;
-    vt[idx] = g;
-    if (vg) {
-        const double dRx[9] = {0, 0, 0, 0, -s[0] * deg, -c[0] * deg, 0, c[0] * deg, -s[0] * deg};
-        const double dRy[9] = {-s[1] * deg, 0, c[1] * deg, 0, 0, 0, -c[1] * deg, 0, -s[1] * deg};
-        const double dRz[9] = {-s[2] * deg, -c[2] * deg, 0, c[2] * deg, -s[2] * deg, 0, 0, 0, 0};
-        double dR[3][9], tmp[9];
-        mat3_mul(Ry, dRx, tmp);
-        mat3_mul(Rz, tmp, dR[0]);
+    return g;
+}
+
+// dP'/dtheta_q and dC/dtheta_q.
+__device__ __forceinline__ void view_derivative(const double *Pv, const ViewGeom &g, const ViewRotation &r, int q,
+                                                double dP[12], double dC[3]) {
+    const double deg = 3.14159265358979323846 / 180.0;
+    const double *c = r.c, *s = r.s;
+    const double Rx[9] = {1, 0, 0, 0, c[0], -s[0], 0, s[0], c[0]};
+    const double dRx[9] = {0, 0, 0, 0, -s[0] * deg, -c[0] * deg, 0, c[0] * deg, -s[0] * deg};
+    const double dRy[9] = {-s[1] * deg, 0, c[1] * deg, 0, 0, 0, -c[1] * deg, 0, -s[1] * deg};
+    const double dRz[9] = {-s[2] * deg, -c[2] * deg, 0, c[2] * deg, -s[2] * deg, 0, 0, 0, 0};
+    double dR[9], tmp[9];
+    if (q == 0) {
+        mat3_mul(r.Ry, dRx, tmp);
+        mat3_mul(r.Rz, tmp, dR);
+    } else if (q == 1) {
         mat3_mul(dRy, Rx, tmp);
-        mat3_mul(Rz, tmp, dR[1]);
-        mat3_mul(dRz, RyRx, dR[2]);
-        ViewGeomGrad gg;
-        for (int q = 0; q < 6; ++q) {
-            for (int i = 0; i < 3; ++i) {
-                for (int j = 0; j < 3; ++j)
-                    gg.dP[q][4 * i + j] =
-                        q < 3 ? Pv[4 * i] * dR[q][j] + Pv[4 * i + 1] * dR[q][3 + j] + Pv[4 * i + 2] * dR[q][6 + j] : 0.0;
-                gg.dP[q][4 * i + 3] = q < 3 ? 0.0 : Pv[4 * i + (q - 3)];
-            }
-            Dual Pd[12], Cd[3];
-            for (int e = 0; e < 12; ++e) Pd[e] = Dual(g.P[e], gg.dP[q][e]);
-            source_position(Pd, Cd);
-            for (int e = 0; e < 3; ++e) gg.dC[q][e] = Cd[e].d;
-        }
-        vg[idx] = gg;
+        mat3_mul(r.Rz, tmp, dR);
+    } else {
+        mat3_mul(dRz, r.RyRx, dR);
     }
+    for (int i = 0; i < 3; ++i) {
+        for (int j = 0; j < 3; ++j)
+            dP[4 * i + j] = q < 3 ? Pv[4 * i] * dR[j] + Pv[4 * i + 1] * dR[3 + j] + Pv[4 * i + 2] * dR[6 + j] : 0.0;
+        dP[4 * i + 3] = q < 3 ? 0.0 : Pv[4 * i + (q - 3)];
+    }
+    Dual Pd[12], Cd[3];
+    for (int e = 0; e < 12; ++e) Pd[e] = Dual(g.P[e], dP[e]);
+    source_position(Pd, Cd);
+    for (int e = 0; e < 3; ++e) dC[e] = Cd[e].d;
+}
+
+// Writes a view's geometry, or with derivatives (vg) its share of them: one
+// thread per (hypothesis, view), six with vg (thread q takes parameter q).
+__device__ __forceinline__ void view_setup(const double *P, const double *intr, const double *theta, int B,
+                                           int n_views, int64_t thread, ViewGeom *vt, ViewGeomGrad *vg) {
+    const int64_t idx = vg ? thread / 6 : thread;
+    const int q = vg ? (int)(thread % 6) : 0;
+    if (idx >= (int64_t)B * n_views) return;
+    const int v = (int)(idx % n_views);
+    const double *Pv = P + (int64_t)v * 12;
+    ViewRotation r;
+    const ViewGeom g = view_geometry(Pv, theta + idx * 6, intr + 3 * v, r);
+    if (q == 0) vt[idx] = g;
+    if (vg) view_derivative(Pv, g, r, q, vg[idx].dP[q], vg[idx].dC[q]);
+}
+
+__global__ __launch_bounds__(64) void view_setup_kernel(const double *__restrict__ P, const double *__restrict__ intr,
+                                                        const double *__restrict__ theta, int B, int n_views,
+                                                        ViewGeom *__restrict__ vt, ViewGeomGrad *__restrict__ vg) {
+    view_setup(P, intr, theta, B, n_views, (int64_t)blockIdx.x * 64 + threadIdx.x, vt, vg);
 }
 
 hipError_t launch_view_setup(const double *P, const double *intr, const double *theta, int B, int n_views,
                              ViewGeom *vt, ViewGeomGrad *vg, hipStream_t s) {
-    const int n = B * n_views;
-    hipLaunchKernelGGL(view_setup_kernel, dim3((n + 255) / 256), dim3(256), 0, s, P, intr, theta, B, n_views, vt, vg);
+    const int64_t n = (int64_t)B * n_views * (vg ? 6 : 1);
+    hipLaunchKernelGGL(view_setup_kernel, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s, P, intr, theta, B, n_views,
+                       vt, vg);
     return hipGetLastError();
 }
 
@@ -101,43 +135,81 @@ hipError_t launch_view_setup(const double *P, const double *intr, const double *
 size_t pair_const_bytes(bool geom64) { return geom64 ? sizeof(PairConst<double>) : sizeof(PairConst<float>); }
 
 // One thread per (hypothesis, pair): the FP64 per-pair geometry -> the pair's
-// per-plane constants, written to a table the plane kernels read with
-// wave-uniform (scalar) loads.
+// per-plane constants, written to a table the plane kernels stage in LDS.
 template <class G>
-__global__ __launch_bounds__(256) void pair_setup_kernel(const float *__restrict__ vscale,
-                                                         const ViewGeom *__restrict__ vt,
-                                                         const double *__restrict__ pinv, EvalConsts ec,
-                                                         PairConst<G> *__restrict__ table) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)ec.B * ec.n_pairs) return;
-    const int hyp = (int)(idx / ec.n_pairs);
-    const int64_t p = idx % ec.n_pairs;
-    int a, b;
-    pair_from_index(p, ec.n_views, a, b);
+__device__ __forceinline__ void pair_table(const ViewGeom &A, const ViewGeom &Bv, int a, int b, int64_t ga, int64_t gb,
+                                           const float *vscale, const double *pinv, const EvalConsts &ec,
+                                           PairConst<G> *out) {
     PairConst<G> pc;
-    const int64_t ga = (int64_t)hyp * ec.n_views + a, gb = (int64_t)hyp * ec.n_views + b;
-    pair_setup<G>(vt[ga], vt[gb], ec, pc, pinv ? pinv + 12 * ga : nullptr,
-                  pinv ? pinv + 12 * gb : nullptr);
+    pair_setup<G>(A, Bv, ec, pc, pinv ? pinv + 12 * ga : nullptr, pinv ? pinv + 12 * gb : nullptr);
     pc.va = a;
     pc.vb = b;
     pc.sa = vscale[a];
     pc.sb = vscale[b];
-    table[idx] = pc;
+    *out = pc;
 }
 
 template <class G>
-static hipError_t launch_pair_setup_t(const float *vscale, const ViewGeom *vt, const double *pinv, EvalConsts ec,
-                                      void *table, hipStream_t s) {
-    const int64_t n = (int64_t)ec.B * ec.n_pairs;
-    hipLaunchKernelGGL(pair_setup_kernel<G>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, vscale, vt, pinv,
-                       ec, (PairConst<G> *)table);
+__global__ __launch_bounds__(64) void pair_setup_kernel(const float *__restrict__ vscale,
+                                                        const ViewGeom *__restrict__ vt,
+                                                        const double *__restrict__ pinv, EvalConsts ec,
+                                                        PairConst<G> *__restrict__ table) {
+    const int64_t idx = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    if (idx >= (int64_t)ec.B * ec.n_pairs) return;
+    const int hyp = (int)(idx / ec.n_pairs);
+    int a, b;
+    pair_from_index(idx % ec.n_pairs, ec.n_views, a, b);
+    const int64_t ga = (int64_t)hyp * ec.n_views + a, gb = (int64_t)hyp * ec.n_views + b;
+    pair_table(vt[ga], vt[gb], a, b, ga, gb, vscale, pinv, ec, table + idx);
+}
+
+// View and pair setup in one launch: the first pair_blocks workgroups take the
+// pairs, each thread working out its two views' geometry by itself; the rest
+// write the views' tables.
+template <class G>
+__global__ __launch_bounds__(64) void setup_kernel(const double *__restrict__ P, const double *__restrict__ intr,
+                                                   const double *__restrict__ theta, const float *__restrict__ vscale,
+                                                   const double *__restrict__ pinv, EvalConsts ec, int pair_blocks,
+                                                   ViewGeom *__restrict__ vt, ViewGeomGrad *__restrict__ vg,
+                                                   PairConst<G> *__restrict__ table) {
+    if ((int)blockIdx.x >= pair_blocks) {
+        view_setup(P, intr, theta, ec.B, ec.n_views, (int64_t)(blockIdx.x - pair_blocks) * 64 + threadIdx.x, vt, vg);
+        return;
+    }
+    const int64_t idx = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    if (idx >= (int64_t)ec.B * ec.n_pairs) return;
+    const int hyp = (int)(idx / ec.n_pairs);
+    int a, b;
+    pair_from_index(idx % ec.n_pairs, ec.n_views, a, b);
+    const int64_t ga = (int64_t)hyp * ec.n_views + a, gb = (int64_t)hyp * ec.n_views + b;
+    ViewRotation r;
+    const ViewGeom A = view_geometry(P + 12 * a, theta + 6 * ga, intr + 3 * a, r);
+    const ViewGeom Bv = view_geometry(P + 12 * b, theta + 6 * gb, intr + 3 * b, r);
+    pair_table(A, Bv, a, b, ga, gb, vscale, pinv, ec, table + idx);
+}
+
+template <class G>
+static hipError_t launch_setup_t(const double *P, const double *intr, const double *theta, const float *vscale,
+                                 const double *pinv, EvalConsts ec, ViewGeom *vt, ViewGeomGrad *vg, void *table,
+                                 hipStream_t s) {
+    const int64_t n = (int64_t)ec.B * ec.n_pairs, pair_blocks = (n + 63) / 64;
+    if (n <= kFusedSetupPairs) {
+        const int64_t n_view = (int64_t)ec.B * ec.n_views * (vg ? 6 : 1);
+        hipLaunchKernelGGL(setup_kernel<G>, dim3((unsigned)(pair_blocks + (n_view + 63) / 64)), dim3(64), 0, s, P, intr,
+                           theta, vscale, pinv, ec, (int)pair_blocks, vt, vg, (PairConst<G> *)table);
+        return hipGetLastError();
+    }
+    hipError_t e = launch_view_setup(P, intr, theta, ec.B, ec.n_views, vt, vg, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(pair_setup_kernel<G>, dim3((unsigned)pair_blocks), dim3(64), 0, s, vscale, (const ViewGeom *)vt,
+                       pinv, ec, (PairConst<G> *)table);
     return hipGetLastError();
 }
 
-hipError_t launch_pair_setup(const float *view_scale, const ViewGeom *vt, EvalConsts ec, void *table, hipStream_t s,
-                             const double *pinv) {
-    return ec.geom64 ? launch_pair_setup_t<double>(view_scale, vt, pinv, ec, table, s)
-                     : launch_pair_setup_t<float>(view_scale, vt, pinv, ec, table, s);
+hipError_t launch_setup(const double *P, const double *intr, const double *theta, const float *view_scale,
+                        const double *pinv, EvalConsts ec, ViewGeom *vt, ViewGeomGrad *vg, void *table, hipStream_t s) {
+    return ec.geom64 ? launch_setup_t<double>(P, intr, theta, view_scale, pinv, ec, vt, vg, table, s)
+                     : launch_setup_t<float>(P, intr, theta, view_scale, pinv, ec, vt, vg, table, s);
 }
 
 // One plane of one pair between issuing its gathers and combining them: the
@@ -193,11 +265,15 @@ __device__ __forceinline__ void combine_plane(const PlaneInFlight<Tap> &P, bool 
 // the hit mask.  The gathers of sweep i + 1 are issued before sweep i is
 // combined, so each wave keeps two planes' gathers in flight.  out_pair and
 // out_count (e and N_kappa per pair) are optional.
-template <class Tap, class G>
+// SUM: the last workgroup of a hypothesis to finish sums its partials into
+// out_cost (reduce_cost), found by a ticket counter that the view setup left
+// at zero (a padding word of the hypothesis's first view).
+template <class Tap, class G, bool SUM>
 __global__ __launch_bounds__(256) void ecc_fwd_kernel(const void *__restrict__ sino,
                                                       const PairConst<G> *__restrict__ table, EvalConsts ec,
                                                       float *__restrict__ out_pair, int32_t *__restrict__ out_count,
-                                                      double *__restrict__ partials, int n_tiles) {
+                                                      double *__restrict__ partials, int n_tiles,
+                                                      ViewGeom *__restrict__ vt, double *__restrict__ out_cost) {
     // the column offset joins an FMA with two other scalar operands: keep it
     // in a vector register for the whole kernel rather than copy it per plane
     asm volatile("" : "+v"(ec.t0_tau));
@@ -303,6 +379,20 @@ __global__ __launch_bounds__(256) void ecc_fwd_kernel(const void *__restrict__ s
             for (int k = 0; k < Q; ++k) sum += part_acc[k * hpb + wave];
             partials[(int64_t)hyp * n_tiles + tile_w] = sum;
         }
+        if constexpr (SUM) {
+            // one hypothesis per workgroup (pair_split): thread 0 wrote its partial
+            __shared__ bool last;
+            if (threadIdx.x == 0) {
+                __threadfence();
+                uint32_t *ticket = (uint32_t *)vt[(int64_t)hyp * ec.n_views].pad;
+                last = atomicAdd(ticket, 1u) == (uint32_t)n_tiles - 1u;
+            }
+            __syncthreads();
+            if (last) {
+                __threadfence();  // the other workgroups' partials
+                reduce_cost<64 * kWavesPerBlock>(partials + (int64_t)hyp * n_tiles, n_tiles, out_cost + hyp);
+            }
+        }
     }
 }
 
@@ -318,48 +408,44 @@ size_t occupancy_lds_bytes(size_t static_bytes, int cap) {
     return b > static_bytes ? b - static_bytes : 0;
 }
 
+__global__ __launch_bounds__(kReduceThreads) void reduce_cost_kernel(const double *__restrict__ partials, int n_tiles,
+                                                                     double *__restrict__ out_cost) {
+    reduce_cost<kReduceThreads>(partials + (int64_t)blockIdx.x * n_tiles, n_tiles, out_cost + blockIdx.x);
+}
+
 template <class Tap, class G>
 static hipError_t launch_fwd_t(const void *sino, const void *table, EvalConsts ec, float *out_pair,
-                               int32_t *out_count, double *partials, int n_tiles, hipStream_t s) {
+                               int32_t *out_count, double *partials, int n_tiles, ViewGeom *vt, double *out_cost,
+                               hipStream_t s) {
     const int64_t total = plane_work_items(ec.B, n_tiles);
     const int64_t blocks = 8 * ((total + 7) / 8);
-    hipLaunchKernelGGL((ecc_fwd_kernel<Tap, G>), dim3((unsigned)blocks), dim3(64 * kWavesPerBlock),
-                       occupancy_lds_bytes(plane_kernel_lds<G>(), kFwdBlocksPerCU),
-                       s, sino, (const PairConst<G> *)table, ec, out_pair, out_count, partials, n_tiles);
+    const bool sum = total <= kTicketItems;
+    const auto kernel = sum ? ecc_fwd_kernel<Tap, G, true> : ecc_fwd_kernel<Tap, G, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * kWavesPerBlock),
+                       occupancy_lds_bytes(plane_kernel_lds<G>(sum), kFwdBlocksPerCU), s, sino,
+                       (const PairConst<G> *)table, ec, out_pair, out_count, partials, n_tiles, vt, out_cost);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || sum) return e;
+    hipLaunchKernelGGL(reduce_cost_kernel, dim3(ec.B), dim3(kReduceThreads), 0, s, (const double *)partials, n_tiles,
+                       out_cost);
     return hipGetLastError();
 }
 
 hipError_t launch_ecc_fwd(const void *sino, const void *table, EvalConsts ec, int dtype, float *out_pair,
-                          int32_t *out_count, double *partials, int n_tiles, hipStream_t s) {
+                          int32_t *out_count, double *partials, int n_tiles, ViewGeom *vt, double *out_cost,
+                          hipStream_t s) {
     if (ec.geom64) {
-        if (dtype == 0) return launch_fwd_t<TapF32, double>(sino, table, ec, out_pair, out_count, partials, n_tiles, s);
-        if (dtype == 1) return launch_fwd_t<TapBF16, double>(sino, table, ec, out_pair, out_count, partials, n_tiles, s);
-        return launch_fwd_t<TapF16, double>(sino, table, ec, out_pair, out_count, partials, n_tiles, s);
+        if (dtype == 0)
+            return launch_fwd_t<TapF32, double>(sino, table, ec, out_pair, out_count, partials, n_tiles, vt, out_cost, s);
+        if (dtype == 1)
+            return launch_fwd_t<TapBF16, double>(sino, table, ec, out_pair, out_count, partials, n_tiles, vt, out_cost, s);
+        return launch_fwd_t<TapF16, double>(sino, table, ec, out_pair, out_count, partials, n_tiles, vt, out_cost, s);
     }
-    if (dtype == 0) return launch_fwd_t<TapF32, float>(sino, table, ec, out_pair, out_count, partials, n_tiles, s);
-    if (dtype == 1) return launch_fwd_t<TapBF16, float>(sino, table, ec, out_pair, out_count, partials, n_tiles, s);
-    return launch_fwd_t<TapF16, float>(sino, table, ec, out_pair, out_count, partials, n_tiles, s);
-}
-
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void reduce_cost_kernel(const double *__restrict__ partials, int n_tiles,
-                                                          double *__restrict__ out_cost) {
-    __shared__ double red[256];
-    const int hyp = blockIdx.x;
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < n_tiles; i += 256) acc += partials[(int64_t)hyp * n_tiles + i];
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out_cost[hyp] = red[0];
-}
-
-hipError_t launch_reduce_cost(const double *partials, int n_tiles, int B, double *out_cost, hipStream_t s) {
-    hipLaunchKernelGGL(reduce_cost_kernel, dim3(B), dim3(256), 0, s, partials, n_tiles, out_cost);
-    return hipGetLastError();
+    if (dtype == 0)
+        return launch_fwd_t<TapF32, float>(sino, table, ec, out_pair, out_count, partials, n_tiles, vt, out_cost, s);
+    if (dtype == 1)
+        return launch_fwd_t<TapBF16, float>(sino, table, ec, out_pair, out_count, partials, n_tiles, vt, out_cost, s);
+    return launch_fwd_t<TapF16, float>(sino, table, ec, out_pair, out_count, partials, n_tiles, vt, out_cost, s);
 }
 
 }  // namespace ecc

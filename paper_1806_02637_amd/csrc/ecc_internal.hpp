@@ -109,20 +109,24 @@ hipError_t launch_view_setup(const double *P, const double *intr, const double *
                              ViewGeom *vt, ViewGeomGrad *vg, hipStream_t s);
 // per-pair constant table: [B][n_pairs] PairConst<float> or PairConst<double>
 size_t pair_const_bytes(bool geom64);
-// pinv (optional): [B][n_views][4][3] pseudo-inverses of the moved P' (the
-// line route the method replaces)
-hipError_t launch_pair_setup(const float *view_scale, const ViewGeom *vt, EvalConsts ec, void *table, hipStream_t s,
-                             const double *pinv = nullptr);
-// out_pair [B][n_pairs] e and out_count [B][n_pairs] N_kappa, each optional
+// the views' geometry (and its derivatives, vg) and the pair table; pinv
+// (optional): [B][n_views][4][3] pseudo-inverses of the moved P' (the line
+// route the method replaces)
+hipError_t launch_setup(const double *P, const double *intr, const double *theta, const float *view_scale,
+                        const double *pinv, EvalConsts ec, ViewGeom *vt, ViewGeomGrad *vg, void *table, hipStream_t s);
+// out_pair [B][n_pairs] e and out_count [B][n_pairs] N_kappa, each optional;
+// out_cost [B]; vt as launch_setup left it
 hipError_t launch_ecc_fwd(const void *sino, const void *table, EvalConsts ec, int dtype, float *out_pair,
-                          int32_t *out_count, double *partials, int n_tiles, hipStream_t s);
+                          int32_t *out_count, double *partials, int n_tiles, ViewGeom *vt, double *out_cost,
+                          hipStream_t s);
 // adjoint: plane kernel -> per-pair sensitivities sens [B][n_pairs][13], then
 // per-pair tangent sweeps -> pair_grad [B][n_pairs][12]
 hipError_t launch_ecc_adj(const void *sino, const void *table, const ViewGeom *vt, const ViewGeomGrad *vg,
                           EvalConsts ec, int dtype, float *sens, float *pair_grad, double *partials, int n_tiles,
                           hipStream_t s);
-hipError_t launch_reduce_cost(const double *partials, int n_tiles, int B, double *out_cost, hipStream_t s);
-hipError_t launch_reduce_grad(const float *pair_grad, int B, int n_views, float *grad, hipStream_t s);
+// the cost's and the gradient's sums in one launch
+hipError_t launch_reduce(const double *partials, int n_tiles, const float *pair_grad, int B, int n_views,
+                         double *out_cost, float *grad, hipStream_t s);
 
 // Akima spline motion model (spline.hip): node positions along the view
 // index, strictly ascending, covering [0, n_views - 1].
@@ -162,6 +166,16 @@ __host__ __device__ inline int pair_subtiles(int B) { return B == 1 ? 8 : (B == 
 // forms at 5 or 6 no faster; the adjoint at 3 is 17 % slower)
 constexpr int kFwdBlocksPerCU = 4;
 constexpr int kAdjBlocksPerCU = 4;
+// evaluations of at most so many (hypothesis, pair)s set up views and pairs in
+// one launch, each thread working out its two views again: 120 pairs 18.8
+// against 22.3 us a cost (a launch less), 30628 pairs 56.1 against 57.4; at
+// 114240 pairs 134.9 against 132.6
+constexpr int64_t kFusedSetupPairs = 32768;
+// evaluations of at most so many work items (one workgroup each) are summed by
+// each hypothesis's last workgroup: a launch less (24 items: 16.4 against 19.6
+// us a cost), but the tickets' fences and atomics take about 47 ns each, one
+// after the other
+constexpr int64_t kTicketItems = 48;
 // dynamic LDS that, added to a kernel's static LDS, caps resident
 // workgroups per CU at `cap` (0 = no cap)
 size_t occupancy_lds_bytes(size_t static_bytes, int cap);

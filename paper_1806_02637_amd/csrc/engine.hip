@@ -732,11 +732,9 @@ static ecc_status cost_impl(ecc_ctx *ctx, int32_t scan_id, int32_t B, const doub
     const EvalConsts ec = make_consts(s, B, params);
     const int n_tiles = n_work_tiles(ec.n_views, B);
     void *table = ws + w.table_off;
-    HIP_TRY(launch_view_setup(s->P_dev, s->intr_dev, theta_dev, B, s->n_views, vt, nullptr, hs));
-    HIP_TRY(launch_pair_setup(s->scale_dev, vt, ec, table, hs, pinv_dev));
-    HIP_TRY(launch_ecc_fwd(s->sino_dev, table, ec, s->layout.dtype, out_pair_dev, out_count_dev, partials, n_tiles,
-                           hs));
-    HIP_TRY(launch_reduce_cost(partials, n_tiles, B, out_cost_dev, hs));
+    HIP_TRY(launch_setup(s->P_dev, s->intr_dev, theta_dev, s->scale_dev, pinv_dev, ec, vt, nullptr, table, hs));
+    HIP_TRY(launch_ecc_fwd(s->sino_dev, table, ec, s->layout.dtype, out_pair_dev, out_count_dev, partials, n_tiles, vt,
+                           out_cost_dev, hs));
     return ok();
 }
 
@@ -792,12 +790,10 @@ ecc_status ecc_cost_grad(ecc_ctx *ctx, int32_t scan_id, int32_t B, const double 
     const EvalConsts ec = make_consts(s, B, params);
     const int n_tiles = n_work_tiles(ec.n_views, B);
     void *table = ws + w.table_off;
-    HIP_TRY(launch_view_setup(s->P_dev, s->intr_dev, theta_dev, B, s->n_views, vt, vg, hs));
-    HIP_TRY(launch_pair_setup(s->scale_dev, vt, ec, table, hs));
+    HIP_TRY(launch_setup(s->P_dev, s->intr_dev, theta_dev, s->scale_dev, nullptr, ec, vt, vg, table, hs));
     float *sens = (float *)(ws + w.sens_off);
     HIP_TRY(launch_ecc_adj(s->sino_dev, table, vt, vg, ec, s->layout.dtype, sens, pgrad, partials, n_tiles, hs));
-    HIP_TRY(launch_reduce_cost(partials, n_tiles, B, out_cost_dev, hs));
-    HIP_TRY(launch_reduce_grad(pgrad, B, s->n_views, grad_dev, hs));
+    HIP_TRY(launch_reduce(partials, n_tiles, pgrad, B, s->n_views, out_cost_dev, grad_dev, hs));
     return ok();
 }
 

@@ -184,11 +184,41 @@ __host__ __device__ inline int64_t plane_work_items(int B, int n_work_tiles) {
     return (int64_t)n_work_tiles * ((B + hpb - 1) / hpb);
 }
 
-// Static LDS of the plane kernels: the pair constants of each wave's tile and
-// the per-wave partial sums.
+// Static LDS of the plane kernels: the pair constants of each wave's tile, the
+// per-wave partial sums and (forward kernel with SUM) the cost's reduction.
 template <class G>
-constexpr size_t plane_kernel_lds() {
-    return sizeof(PairConst<G>) * kPairsPerWave * kWavesPerBlock + sizeof(double) * kWavesPerBlock;
+constexpr size_t plane_kernel_lds(bool sum = false) {
+    return sizeof(PairConst<G>) * kPairsPerWave * kWavesPerBlock + sizeof(double) * kWavesPerBlock +
+           (sum ? sizeof(double) * 64 * kWavesPerBlock + 16 : 0);
+}
+
+// Sum of a hypothesis's partials in a fixed order (Eq. 17), by one workgroup
+// of THREADS.  Each thread keeps eight loads in flight: with one workgroup per
+// hypothesis the reduction is the latency of its loads (15624 partials: 23 us
+// by 256 threads taking one load at a time, 6 us so).
+constexpr int kReduceThreads = 512;
+template <int THREADS>
+__device__ __forceinline__ void reduce_cost(const double *p, int n_tiles, double *out) {
+    __shared__ double red[THREADS];
+    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int i = threadIdx.x; i < n_tiles; i += 8 * THREADS) {
+        double x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = i + k * THREADS < n_tiles ? p[i + k * THREADS] : 0.0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[k] += x[k];
+    }
+    red[threadIdx.x] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+    __syncthreads();
+    for (int w = THREADS / 2; w >= 64; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x < 64) {
+        double s = red[threadIdx.x];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (threadIdx.x == 0) *out = s;
+    }
 }
 
 // Logical work item of a block under the XCD-aware numbering.

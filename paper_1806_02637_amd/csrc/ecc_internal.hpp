@@ -160,12 +160,15 @@ constexpr int kWavesPerBlock = 4;
 // better).  The plane kernels take the number of work tiles, pair tiles *
 // pair_subtiles(B), and write one partial sum per hypothesis and work tile.
 __host__ __device__ inline int pair_subtiles(int B) { return B == 1 ? 8 : (B == 2 ? 4 : 2); }
-// caps on resident plane-kernel workgroups per CU (0 = no cap), 4 for the
-// forward kernel with every storage form and for the adjoint (at B = 32 on
-// the 496-view scan: the FP32 forward kernel at 3 is 2 % slower, the 16-bit
-// forms at 5 or 6 no faster; the adjoint at 3 is 17 % slower)
+// caps on resident plane-kernel workgroups per CU (0 = no cap): 4 for the
+// forward kernel with every storage form (at B = 32 on the 496-view scan FP32 at
+// 3 is 2 % slower, the 16-bit forms at 5 or 6 no faster; at B = 1 5 to 7 are no
+// faster).  The adjoint waits for its gathers (no plane ahead of the one it
+// works on), so it takes 6: cost + gradient at B = 1 470 against 490 us with 4
+// (496 views), 71.7 against 76.0 (248 views), 196.5 against 205.8 at B = 4,
+// 10.97 against 11.00 ms at B = 32.
 constexpr int kFwdBlocksPerCU = 4;
-constexpr int kAdjBlocksPerCU = 4;
+constexpr int kAdjBlocksPerCU = 6;
 // evaluations of at most so many (hypothesis, pair)s set up views and pairs in
 // one launch, each thread working out its two views again: 120 pairs 18.8
 // against 22.3 us a cost (a launch less), 30628 pairs 56.1 against 57.4; at

@@ -102,8 +102,8 @@ hipError_t launch_sino_radon_gather(const float *gw, const float *gwT, const dou
                                     int n_alpha, int n_t, double ds, double *G, hipStream_t s);
 hipError_t launch_sino_store(const double *G, const float *ext, int n_views, int n_alpha, int n_t, double dt,
                              int dtype, void *sino, float *view_scale, uint32_t *view_absmax, hipStream_t s);
-hipError_t launch_sino_read(const void *sino, const float *view_scale, SinoLayout L, int view, float *out,
-                            hipStream_t s);
+hipError_t launch_sino_read(const void *sino, const float *view_scale, SinoLayout L, int view, int m0, int rows,
+                            float *out, hipStream_t s);
 
 hipError_t launch_view_setup(const double *P, const double *intr, const double *theta, int B, int n_views,
                              ViewGeom *vt, ViewGeomGrad *vg, hipStream_t s);

@@ -700,10 +700,12 @@ hipError_t launch_sino_store(const double *G, const float *ext, int n_views, int
 }
 
 // ---------------------------------------------------------------------------
+// Decodes rows m0 .. of one view's sinogram.  out may be pinned host memory:
+// lanes along t, so a wavefront stores 256 contiguous bytes over the link.
 __global__ __launch_bounds__(256) void sino_read_kernel(const void *sino, const float *view_scale, SinoLayout L,
-                                                        int v, float *out) {
+                                                        int v, int m0, float *out) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    const int m = blockIdx.y;  // 0..n_alpha
+    const int m = m0 + blockIdx.y;  // 0..n_alpha
     if (k >= L.n_t) return;
     const int mr = m < L.n_alpha ? m : L.n_alpha - 1;
     const int half = m < L.n_alpha ? 0 : 1;
@@ -720,13 +722,13 @@ __global__ __launch_bounds__(256) void sino_read_kernel(const void *sino, const 
         else
             val = (float)__builtin_bit_cast(_Float16, h);
     }
-    out[(int64_t)m * L.n_t + k] = val * view_scale[v];
+    out[(int64_t)blockIdx.y * L.n_t + k] = val * view_scale[v];
 }
 
-hipError_t launch_sino_read(const void *sino, const float *view_scale, SinoLayout L, int view, float *out,
-                            hipStream_t s) {
-    dim3 grid((L.n_t + 255) / 256, L.n_alpha + 1, 1);
-    hipLaunchKernelGGL(sino_read_kernel, grid, dim3(256), 0, s, sino, view_scale, L, view, out);
+hipError_t launch_sino_read(const void *sino, const float *view_scale, SinoLayout L, int view, int m0, int rows,
+                            float *out, hipStream_t s) {
+    dim3 grid((L.n_t + 255) / 256, rows, 1);
+    hipLaunchKernelGGL(sino_read_kernel, grid, dim3(256), 0, s, sino, view_scale, L, view, m0, out);
     return hipGetLastError();
 }
 

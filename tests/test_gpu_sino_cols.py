@@ -68,3 +68,30 @@ def test_non_finite_pixels_reach_the_same_lines(eng):
     assert np.array_equal(np.isfinite(cols[:11]), finite)
     scale = np.abs(gather[finite]).max()
     assert np.abs(cols[:11][finite] - gather[finite]).max() <= 2e-5 * scale
+
+
+@pytest.mark.parametrize("n_alpha,n_t,dtype", [
+    (300, 4099, "f32"),    # more rows than the staging ring holds
+    (2, 65536, "f32"),     # the longest rows
+    (5000, 211, "bf16"),   # a ring and a remainder
+    (3, 3, "f16"),         # a few values
+])
+@pytest.mark.parametrize("pinned", [False, True])
+def test_read_returns_the_stored_values(eng, n_alpha, n_t, dtype, pinned):
+    """A sinogram read back is the stored one: row by row the values given,
+    rounded to the storage type at the view's scale (FP32: two roundings)."""
+    import torch
+
+    from paper_1806_02637_amd import binding as B
+
+    print(f"case: read {n_alpha + 1}x{n_t} {dtype} pinned {pinned}", flush=True)
+    sino = np.random.default_rng(n_t).uniform(-1.0, 1.0, (2, n_alpha + 1, n_t)).astype(np.float32)
+    g = inputs.ScanGeometry(2, 64, 48, 5.0)
+    scan = eng.load_scan(g.projection_matrices(), g.intrinsics(), np.zeros((2, 48, 64), np.float32))
+    scan.set_sinograms(sino, dtype)
+    bar = {"f32": 2.0 ** -22, "bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype]
+    for v in (1, 0):
+        t = torch.full((n_alpha + 1, n_t), np.nan, pin_memory=pinned)
+        B.ecc_scan_read_sinogram(scan.ctx, scan.id, v, t.data_ptr())
+        assert np.abs(t.numpy() - sino[v]).max() <= bar, v
+    scan.free()

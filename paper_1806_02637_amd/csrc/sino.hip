@@ -321,8 +321,8 @@ __device__ __noinline__ double radon_line_direct(const float4 *img, int c4, int 
 // waves compute the (lane, line slot) weights together, kCols / waves columns
 // each, into LDS, between the columns of the chunk before; every wave walks
 // the columns, V / 4 coalesced 16-byte loads and V NL multiply-adds per
-// column.  The sums of kCols columns are taken in FP32, then added to FP64
-// totals; at the strip's end each line adds its lanes' totals in lane order.
+// column.  The sums of up to kCols columns are taken in FP32, then added to
+// FP64 totals; at the strip's end each line adds its lanes' totals in lane order.
 //
 // On 496 views of 1240 x 960 (768 x 1024 lines, 0.5 px samples) the build's
 // line sums take 115 ms against 388 ms by gathered samples (60 views of
@@ -342,7 +342,7 @@ constexpr int kRadonWaves = 4;
 template <int NL, int V, int MT>
 __global__ __launch_bounds__(64 * kRadonWaves, NL <= 3 ? 3 : 2) void sino_radon_kernel(
     const float4 *__restrict__ gw, const float4 *__restrict__ gwT, int n_views, int W, int H, int n_alpha, int n_t,
-    double t_max, double dt, double ds, int n_s, int R, int n_strips, double *__restrict__ G) {
+    double t_max, double dt, double ds, int n_s, int R, int n_strips, int part_mask, double *__restrict__ G) {
     static_assert(sizeof(float) * 2 * kCols * NL * 64 >= sizeof(double) * kRadonWaves * NL * 64,
                   "the totals reuse the weights' LDS");
     __shared__ __align__(16) float wbuf[2][kCols][NL][64];
@@ -490,15 +490,16 @@ __global__ __launch_bounds__(64 * kRadonWaves, NL <= 3 ? 3 : 2) void sino_radon_
                 load_column(x[d]);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if (((i + kAhead) & part_mask) != 0 && i + kAhead < n_cols) continue;
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+#pragma unroll
+                for (int l = 0; l < NL; ++l) {
+                    tot[v][l] += (double)acc[v][l];
+                    acc[v][l] = 0.0f;
+                }
         }
         for (; next < kCols; next += n_waves) weights(p0 + kCols + next, wbuf[buf ^ 1][next]);
-#pragma unroll
-        for (int v = 0; v < V; ++v)
-#pragma unroll
-            for (int l = 0; l < NL; ++l) {
-                tot[v][l] += (double)acc[v][l];
-                acc[v][l] = 0.0f;
-            }
     }
     __syncthreads();  // the weights are read; their LDS takes the totals
     double(*red)[64] = (double(*)[64])((double *)wbuf + (size_t)wave * NL * 64);
@@ -533,6 +534,18 @@ __global__ __launch_bounds__(64 * kRadonWaves, NL <= 3 ? 3 : 2) void sino_radon_
     }
 }
 
+// Columns (a power of two, up to kCols) summed in FP32 before they go to the
+// FP64 totals: short sums for small detectors, whose lines have few of them to
+// average over.  Relative error of a sinogram against 64 bits (rms, 1e-7), here
+// | with 16 columns throughout | of the gathered samples: 122 x 98 1.2 | 2.8 |
+// 1.2, 207 x 160 1.5 | 3.4 | 2.2, 280 x 191 2.6 | 4.2 | 3.0, 429 x 264 2.9 | 4.8
+// | 4.4, 525 x 326 5.7 | 5.7 | 6.2.  On 496 views of 1240 x 960 sums of 4 cost
+// 10 % of the build, of 2 20 %.
+static int radon_part_columns(int W, int H) {
+    const int64_t pixels = (int64_t)W * H;
+    return pixels >= 160000 ? 16 : pixels >= 45000 ? 8 : pixels >= 16000 ? 4 : 2;
+}
+
 template <int NL, int V>
 static hipError_t launch_radon_t(const float4 *gw, const float4 *gwT, int n_views, int W, int H, int n_alpha, int n_t,
                                  double t_max, double dt, double ds, int n_s, int R, double *G, hipStream_t s) {
@@ -553,7 +566,7 @@ static hipError_t launch_radon_t(const float4 *gw, const float4 *gwT, int n_view
                         : ds >= 0.4715 ? sino_radon_kernel<NL, V, 3>
                                        : sino_radon_kernel<NL, V, 0>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * waves), 0, s, gw, gwT, n_views, W, H,
-                       n_alpha, n_t, t_max, dt, ds, n_s, R, strips, G);
+                       n_alpha, n_t, t_max, dt, ds, n_s, R, strips, radon_part_columns(W, H) - 1, G);
     return hipGetLastError();
 }
 
@@ -562,10 +575,14 @@ static hipError_t launch_radon_t(const float4 *gw, const float4 *gwT, int n_view
 // (build of N views, 620 x 480, 512 lines): N = 8 1.69 against 1.22 ms by
 // gathered samples, N = 12 1.21 against 2.03, N = 16 1.55 against 2.89, N = 32
 // 1.9 against 5.1.  Line spacing (16 views, 1240 x 960): 6 px 3.3 against 6.0
-// ms, 12 px 3.4 against 4.6, 20 px 3.4 against 3.4.  Element offsets are 32-bit.
+// ms, 12 px 3.4 against 4.6, 20 px 3.4 against 3.4.  Small scans are over before
+// the strips' serial walk of their columns is: 64 x 48 pixels 60 against 46 us
+// with 20 views (61 K pixels in all), 65 against 66 with 48 (147 K); 115 x 100 95 against
+// 76 with 12 (138 K), 152 against 149 with 16 (184 K), 143 against 159 with 20
+// (230 K); 160 x 128 153 against 198 with 12 (246 K).  Element offsets are 32-bit.
 bool radon_by_columns(int n_views, int W, int H, int n_t) {
     const double dt = sqrt((double)W * W + (double)H * H) / (n_t - 1);
-    return n_views >= 12 && dt <= 20.0 && (int64_t)W * H < (1ll << 27);
+    return n_views >= 12 && (int64_t)n_views * W * H >= 200000 && dt <= 20.0 && (int64_t)W * H < (1ll << 27);
 }
 
 hipError_t launch_sino_radon(const float *images, const double *intr, int n_views, int W, int H, int n_alpha, int n_t,

@@ -33,15 +33,19 @@ def _build(eng, images, W, H, n_alpha, n_t, ds):
 
 
 @pytest.mark.parametrize("n_views,W,H,n_alpha,n_t,ds", [
-    (13, 70, 50, 24, 40, 0.5),    # 2 lines per lane
-    (17, 97, 61, 20, 75, 0.7),    # 3
-    (12, 64, 64, 20, 91, 1.0),    # 4
+    (61, 70, 50, 24, 40, 0.5),    # 2 lines per lane
+    (35, 97, 61, 20, 75, 0.7),    # 3
+    (49, 64, 64, 20, 91, 1.0),    # 4
     (33, 61, 130, 18, 200, 0.3),  # 5 to 6, many samples per column
-    (12, 48, 40, 16, 300, 0.5),   # interleaved sets of lines
-    (14, 2, 3, 8, 5, 1.0),        # a detector of a few pixels
-    (37, 300, 9, 16, 240, 0.5),   # a wide, low detector
-    (11, 64, 64, 20, 91, 0.5),    # too few views: gathered samples
-    (12, 64, 64, 20, 4, 0.5),     # lines 30 px apart: gathered samples
+    (105, 48, 40, 16, 300, 0.5),  # interleaved sets of lines
+    (75, 300, 9, 16, 240, 0.5),   # a wide, low detector, smaller than a strip
+    (12, 161, 110, 12, 90, 0.5),  # sums of 4, 8 and 16 columns
+    (12, 251, 190, 10, 120, 0.5),
+    (12, 450, 360, 8, 130, 0.5),
+    (11, 161, 130, 12, 91, 0.5),  # too few views: gathered samples
+    (48, 64, 64, 20, 91, 0.5),    # too few pixels: gathered samples
+    (14, 2, 3, 8, 5, 1.0),        # a detector of a few pixels: gathered samples
+    (50, 64, 64, 20, 4, 0.5),     # lines 30 px apart: gathered samples
 ])
 def test_build_matches_oracle(eng, n_views, W, H, n_alpha, n_t, ds):
     print(f"case: build {n_views} views {W}x{H} -> {n_alpha}x{n_t} ds {ds}", flush=True)
@@ -55,19 +59,19 @@ def test_build_matches_oracle(eng, n_views, W, H, n_alpha, n_t, ds):
 
 def test_non_finite_pixels_reach_the_same_lines(eng):
     """NaN and infinite pixels spoil the lines whose samples touch them and no
-    others, as in a build of fewer views (gathered samples)."""
+    others, as in a build of fewer pixels (gathered samples)."""
     print("case: build with non-finite pixels", flush=True)
-    images = np.random.default_rng(3).uniform(0.0, 50.0, (12, 60, 80)).astype(np.float32)
+    images = np.random.default_rng(3).uniform(0.0, 50.0, (42, 60, 80)).astype(np.float32)
     images[2, 20, 31] = np.nan
     images[3, 0, 79] = np.inf
     images[5, 59, 0] = -np.inf
     _, cols = _build(eng, images, 80, 60, 24, 64, 0.5)
-    _, gather = _build(eng, images[:11], 80, 60, 24, 64, 0.5)
+    _, gather = _build(eng, images[:41], 80, 60, 24, 64, 0.5)
     finite = np.isfinite(gather)
     assert not finite.all() and finite.mean() > 0.5
-    assert np.array_equal(np.isfinite(cols[:11]), finite)
+    assert np.array_equal(np.isfinite(cols[:41]), finite)
     scale = np.abs(gather[finite]).max()
-    assert np.abs(cols[:11][finite] - gather[finite]).max() <= 2e-5 * scale
+    assert np.abs(cols[:41][finite] - gather[finite]).max() <= 2e-5 * scale
 
 
 @pytest.mark.parametrize("n_alpha,n_t,dtype", [

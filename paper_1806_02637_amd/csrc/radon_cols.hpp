@@ -133,11 +133,18 @@ ECC_RADON_HD double radon_end_zone(int P, int Q) {
 
 ECC_RADON_HD float radon_tent(float x) { return fminf(fmaxf(1.0f - fabsf(x), 0.0f), 1.0f); }
 
-// 32-bit fraction of a real number.
-ECC_RADON_HD uint32_t fraction_bits(double x) {
+// Samples of a line that can meet a pixel: the fewest N with N / 2 >= 1 / |h|.
+// They lie at psi + e, e = (1 - N) / 2 ... (N - 1) / 2, in steps of the sample
+// index from the pixel's column, |psi| <= 1/2 (odd N: psi from the nearest
+// sample; even N: from the middle between two).
+ECC_RADON_HD int radon_samples(double inv_h) { return (int)ceil(2.0 * fabs(inv_h) - 1e-9); }
+
+// psi + 1/2 as a 32-bit fraction; its sign-extended value in units of 2^-32.
+ECC_RADON_HD uint32_t psi_bits(double index, int N) {
+    const double x = (N & 1) ? index + 0.5 : index;
     return (uint32_t)(int64_t)floor((x - floor(x)) * 4294967296.0);
 }
-ECC_RADON_HD float fraction_value(uint32_t b) { return (float)b * 2.3283064365386963e-10f; }
+ECC_RADON_HD float psi_value(uint32_t b) { return (float)(int32_t)(b ^ 0x80000000u); }
 
 // A pixel's q-offset from a line (|x| < 8) in units of 2^-28 px: kept as an
 // integer until the column's fraction is taken off, since a rounding that
@@ -145,24 +152,56 @@ ECC_RADON_HD float fraction_value(uint32_t b) { return (float)b * 2.328306436538
 ECC_RADON_HD int offset_bits(double x) { return (int)rint(x * 268435456.0); }
 ECC_RADON_HD float offset_value(int b) { return (float)b * 3.7252902984619140625e-9f; }
 
-// Weight of a pixel for a line: b = its q-offset from the line in its column,
-// phi = the fraction of the sample index at the column, samples at
-// phi + m, m = -M .. M - 1 (M >= 1 / |h|).  With ENDS only the samples
-// first + M - 1 - m ... inside [0, n_s) count, first = floor(index) + 1 - M.
-template <int M_FIXED, bool ENDS>
-ECC_RADON_HD float radon_weight(float b, float phi, float s, float h, int M_dyn, int index, int n_s) {
-    const int M = M_FIXED > 0 ? M_FIXED : M_dyn;
+// One angle's constants of the weights with N samples: |h| and s h in units of
+// psi_value, and per sample 1 - |h e| and s h e.
+template <int N>
+struct RadonSteps {
+    float u, v, c[(N + 1) / 2], d[N];
+};
+template <int N>
+ECC_RADON_HD RadonSteps<N> radon_steps(double s, double h) {
+    RadonSteps<N> r;
+    r.u = (float)(fabs(h) * 2.3283064365386963e-10);
+    r.v = (float)(s * h * 2.3283064365386963e-10);
+    for (int i = 0; i < (N + 1) / 2; ++i) r.c[i] = (float)(1.0 - fabs(h) * (0.5 * (N - 1) - i));
+    for (int i = 0; i < N; ++i) r.d[i] = (float)(s * h * (i - 0.5 * (N - 1)));
+    return r;
+}
+
+// Weight of a pixel for a line: offset = the pixel's q-offset from the line in
+// its column, psi = psi_value.  e is never of the other sign than psi + e, so
+// the p-tents are 1 - |h e| -+ |h| psi without an absolute value.  With ENDS
+// only the samples inside [0, n_s) count, the first (e lowest) being `index`.
+template <bool ENDS, int N>
+ECC_RADON_HD float radon_weight(float offset, float psi, const RadonSteps<N> &r, int index, int n_s) {
+    const float u = r.u * psi, y0 = fmaf(r.v, psi, offset);
     float w = 0.0f;
-    const float x0 = phi * h, y0 = fmaf(s, x0, b), hs = s * h;
 #pragma unroll
-    for (int m = -M; m < M; ++m) {
-        // p and q offsets of the pixel from sample j = index - m
-        const float x = fmaf((float)m, h, x0), y = fmaf((float)m, hs, y0);
-        float ww = radon_tent(x) * radon_tent(y);
-        if (ENDS) ww = (index - m >= 0 && index - m < n_s) ? ww : 0.0f;
-        w += ww;
+    for (int i = 0; i < N; ++i) {
+        const float t = 2 * i + 1 < N ? r.c[i] + u : 2 * i + 1 > N ? r.c[N - 1 - i] - u : 1.0f - fabsf(u);
+        const float tp = fminf(fmaxf(t, 0.0f), 1.0f);
+        float tq = radon_tent(2 * i + 1 == N ? y0 : y0 + r.d[i]);
+        if (ENDS) tq = (index - i >= 0 && index - i < n_s) ? tq : 0.0f;
+        w = i == 0 ? tp * tq : fmaf(tp, tq, w);
     }
     return w;
 }
+
+// Any number of samples (steps below 0.47 px), the constants worked out as it goes.
+template <bool ENDS>
+ECC_RADON_HD float radon_weight_any(float offset, float psi, float s, float h, int N, int index, int n_s) {
+    const float f = psi * 2.3283064365386963e-10f;
+    float w = 0.0f;
+    for (int i = 0; i < N; ++i) {
+        const float x = h * (f + ((float)i - 0.5f * (float)(N - 1)));
+        float tq = radon_tent(fmaf(s, x, offset));
+        if (ENDS) tq = (index - i >= 0 && index - i < n_s) ? tq : 0.0f;
+        w = fmaf(radon_tent(x), tq, w);
+    }
+    return w;
+}
+
+// Index of the first sample (e lowest) of the N that can meet the pixel.
+ECC_RADON_HD int radon_first_sample(double index, int N) { return (int)floor((N & 1) ? index + 0.5 : index) + N / 2; }
 
 }  // namespace ecc

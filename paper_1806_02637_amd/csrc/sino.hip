@@ -325,20 +325,33 @@ __device__ __noinline__ double radon_line_direct(const float4 *img, int c4, int 
 // FP64 totals; at the strip's end each line adds its lanes' totals in lane order.
 //
 // On 496 views of 1240 x 960 (768 x 1024 lines, 0.5 px samples) the build's
-// line sums take 115 ms against 388 ms by gathered samples (60 views of
-// 620 x 480, 360 x 512 lines: 1.93 against 7.97 ms).  Gathered samples were
+// line sums take 114 ms against 388 ms by gathered samples (60 views of
+// 620 x 480, 360 x 512 lines: 1.86 against 7.97 ms).  Gathered samples were
 // bound by the texture data path: a 16-byte gather and 15 instructions per
 // sample, 1.3 samples per pixel and angle.  Here a pixel costs 4 loaded bytes
-// and 8.2 instructions per view and angle (3 multiply-adds, 3.9 for its share
-// of the weights, the rest addresses and the FP64 sums): the issue slots are
-// full (SQ_INSTS_VALU x 4 cycles / SIMD cycles 1.1) and the texture data path
-// is busy 93 % of the cycles.  8 waves or 16 views per wave halve the weights'
+// and 7.3 instructions per view and angle (3 multiply-adds, 2.9 for its share
+// of the weights, the rest addresses and the FP64 sums; 8.2, and 120 and 1.98
+// ms, with 6 samples of two clamped tents each at every angle): the issue slots
+// are full to 95 % (SQ_INSTS_VALU x 4 cycles) and the texture data path is busy
+// 92 % of the cycles.  8 waves or 16 views per wave halve the weights'
 // share but leave more views' pixels in flight than the L2 holds (131 and
 // 131 ms); 32-column chunks measure the same and sum less precisely.
 constexpr int kCols = 16;
 constexpr int kAhead = 2;  // columns of loads in flight (1: 145 ms, 4: 126 ms)
 constexpr int kRadonWaves = 4;
 
+// The steps in scalar registers.
+template <int N>
+__device__ __forceinline__ RadonSteps<N> uniform(RadonSteps<N> r) {
+    r.u = uniform_f(r.u);
+    r.v = uniform_f(r.v);
+    for (float &x : r.c) x = uniform_f(x);
+    for (float &x : r.d) x = uniform_f(x);
+    return r;
+}
+
+// MT: the most samples of a line that can meet a pixel (0: any number); the
+// angles where MT - 1 suffice (most of them) sum that many.
 template <int NL, int V, int MT>
 __global__ __launch_bounds__(64 * kRadonWaves, NL <= 3 ? 3 : 2) void sino_radon_kernel(
     const float4 *__restrict__ gw, const float4 *__restrict__ gwT, int n_views, int W, int H, int n_alpha, int n_t,
@@ -382,6 +395,8 @@ __global__ __launch_bounds__(64 * kRadonWaves, NL <= 3 ? 3 : 2) void sino_radon_
     strip_columns(g, strip, p_lo, p_hi);
     p_lo = __builtin_amdgcn_readfirstlane(p_lo);
     p_hi = __builtin_amdgcn_readfirstlane(p_hi);
+    const int N_min = __builtin_amdgcn_readfirstlane(radon_samples(g.inv_h));
+    const int N = MT > 0 ? max(min(N_min, MT), MT - 1) : N_min;
     // this lane's lines
     const int first = lane_first_line(g, Q0, lane);
     int bq[NL];
@@ -389,11 +404,13 @@ __global__ __launch_bounds__(64 * kRadonWaves, NL <= 3 ? 3 : 2) void sino_radon_
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
         bq[l] = offset_bits(Q0 + lane - (g.kappa0 + (first + l) * g.dkappa));
-        ph0[l] = fraction_bits(sample_at(g, first + l, 0.0, c));
+        ph0[l] = psi_bits(sample_at(g, first + l, 0.0, c), N);
     }
-    const uint32_t ph_step = fraction_bits(g.inv_h);
+    const uint32_t ph_step = psi_bits(g.inv_h, 0);
     const float sf = uniform_f((float)g.s), hf = uniform_f((float)g.h);
-    const int M = MT > 0 ? MT : __builtin_amdgcn_readfirstlane((int)ceil(fabs(g.inv_h)));
+    constexpr int kMost = MT > 0 ? MT : 2;
+    const RadonSteps<kMost> steps = uniform(radon_steps<kMost>(g.s, g.h));
+    const RadonSteps<kMost - 1> fewer = uniform(radon_steps<kMost - 1>(g.s, g.h));
     const float zone = uniform_f((float)radon_end_zone(g.P, g.Q)), pcf = uniform_f((float)pc);
     // 32.32 fixed-point shear q of lane 0 in column p
     const int64_t sh_step = uniform_i64(to_fixed(g.s));
@@ -411,19 +428,33 @@ __global__ __launch_bounds__(64 * kRadonWaves, NL <= 3 ? 3 : 2) void sino_radon_
         const int q = (int)(sh >> 32) + lane;
         const int fr = (int)((uint32_t)sh >> 4);
         const bool inside = q >= 0 && q < Q && p < p_hi;
-        const bool ends = fabsf((float)p - pcf) >= zone;
+        const bool ends = fabsf((float)p - pcf) >= zone;  // uniform
+        // fn(offset, psi, ends, first sample's index)
+        auto each = [&](auto fn) {
 #pragma unroll
-        for (int l = 0; l < NL; ++l) {
-            const float phi = fraction_value(ph0[l] + (uint32_t)p * ph_step);
-            const float b = offset_value(bq[l] - fr);
-            float w;
-            if (ends) {
-                const int index = (int)floor(sample_at(g, first + l, (double)p, c));
-                w = radon_weight<MT, true>(b, phi, sf, hf, M, index, n_s);
-            } else {
-                w = radon_weight<MT, false>(b, phi, sf, hf, M, 0, 0);
+            for (int l = 0; l < NL; ++l) {
+                const float psi = psi_value(ph0[l] + (uint32_t)p * ph_step);
+                const float b = offset_value(bq[l] - fr);
+                const int index = ends ? radon_first_sample(sample_at(g, first + l, (double)p, c), N) : 0;
+                out[l][lane] = inside ? fn(b, psi, index) : 0.0f;
             }
-            out[l][lane] = inside ? w : 0.0f;
+        };
+        auto take = [&](const auto &r) {
+            if (ends)
+                each([&](float b, float psi, int index) { return radon_weight<true>(b, psi, r, index, n_s); });
+            else
+                each([&](float b, float psi, int) { return radon_weight<false>(b, psi, r, 0, 0); });
+        };
+        if constexpr (MT > 0) {
+            if (N == MT)
+                take(steps);
+            else
+                take(fewer);
+        } else {
+            each([&](float b, float psi, int index) {
+                return ends ? radon_weight_any<true>(b, psi, sf, hf, N, index, n_s)
+                            : radon_weight_any<false>(b, psi, sf, hf, N, 0, 0);
+            });
         }
     };
 
@@ -561,9 +592,10 @@ static hipError_t launch_radon_t(const float4 *gw, const float4 *gwT, int n_view
         strips = strips > n ? strips : n;
     }
     const int64_t blocks = (int64_t)groups * R * strips * 8 * ((n_alpha + 7) / 8);
-    // samples within a pixel of a column: at most 2 ceil(sqrt(2) / ds)
-    const auto kernel = ds >= 0.7072   ? sino_radon_kernel<NL, V, 2>
-                        : ds >= 0.4715 ? sino_radon_kernel<NL, V, 3>
+    // samples within a pixel of a column: at most ceil(2 sqrt(2) / ds)
+    const auto kernel = ds >= 0.7072   ? sino_radon_kernel<NL, V, 4>
+                        : ds >= 0.5657 ? sino_radon_kernel<NL, V, 5>
+                        : ds >= 0.4715 ? sino_radon_kernel<NL, V, 6>
                                        : sino_radon_kernel<NL, V, 0>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * waves), 0, s, gw, gwT, n_views, W, H,
                        n_alpha, n_t, t_max, dt, ds, n_s, R, strips, radon_part_columns(W, H) - 1, G);

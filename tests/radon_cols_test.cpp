@@ -36,6 +36,30 @@ static double direct(const std::vector<float> &img, int W, int H, double sa, dou
         }                                                                     \
     } while (0)
 
+// Samples summed and the weight as the kernel chooses them.
+static int n_weight(const RadonAngle &g) {
+    const double ds = fabs(g.h) * sqrt(1.0 + g.s * g.s);
+    const int N = radon_samples(g.inv_h), MT = ds >= 0.7072 ? 4 : ds >= 0.5657 ? 5 : ds >= 0.4715 ? 6 : 0;
+    return MT > 0 ? std::max(std::min(N, MT), MT - 1) : N;
+}
+template <int N>
+static float weight_n(const RadonAngle &g, float b, float psi, bool ends, int index, int n_s) {
+    const RadonSteps<N> r = radon_steps<N>(g.s, g.h);
+    return ends ? radon_weight<true>(b, psi, r, index, n_s) : radon_weight<false>(b, psi, r, 0, 0);
+}
+static float weight(const RadonAngle &g, int N, float b, float psi, bool ends, int index, int n_s) {
+    const double ds = fabs(g.h) * sqrt(1.0 + g.s * g.s);
+    if (ds < 0.4715)
+        return ends ? radon_weight_any<true>(b, psi, (float)g.s, (float)g.h, N, index, n_s)
+                    : radon_weight_any<false>(b, psi, (float)g.s, (float)g.h, N, 0, 0);
+    switch (N) {
+    case 3: return weight_n<3>(g, b, psi, ends, index, n_s);
+    case 4: return weight_n<4>(g, b, psi, ends, index, n_s);
+    case 5: return weight_n<5>(g, b, psi, ends, index, n_s);
+    default: return weight_n<6>(g, b, psi, ends, index, n_s);
+    }
+}
+
 static int run(int W, int H, int n_alpha, int n_t, double ds, double &worst) {
     std::vector<float> img((size_t)W * H);
     for (auto &x : img) x = (float)(0.2 + rand() / (double)RAND_MAX);
@@ -51,7 +75,8 @@ static int run(int W, int H, int n_alpha, int n_t, double ds, double &worst) {
         for (int r = 0; r < R; ++r) {
             const RadonAngle g = radon_angle(sa, ca, W, H, n_t, t_max, dt, ds, r, R);
             const double pc = 0.5 * (g.P - 1), zone = radon_end_zone(g.P, g.Q);
-            const int M = (int)ceil(1.0 / fabs(g.h));
+            const int N_min = radon_samples(g.inv_h);
+            CHECK(0.5 * N_min >= fabs(g.inv_h) - 1e-9 && 0.5 * N_min < fabs(g.inv_h) + 0.5);
             for (int j = 0; strip_first_line(g, j) < g.n_lines; ++j) {
                 const double Q0 = g.origin0 + (double)j * g.stride;
                 const int k_lo = strip_first_line(g, j), k_hi = strip_first_line(g, j + 1);
@@ -71,11 +96,9 @@ static int run(int W, int H, int n_alpha, int n_t, double ds, double &worst) {
                         for (int k = first - 3; k < first + NL + 3; ++k) {
                             const double b = q - (g.kappa0 + k * g.dkappa) - sh;
                             const double tau = sample_at(g, k, p, c);
-                            const int idx = (int)floor(tau);
-                            const float phi = fraction_value(fraction_bits(tau));
-                            const float w = fabs(p - pc) >= zone
-                                                ? radon_weight<0, true>((float)b, phi, (float)g.s, (float)g.h, M, idx, n_s)
-                                                : radon_weight<0, false>((float)b, phi, (float)g.s, (float)g.h, M, idx, n_s);
+                            const int N = n_weight(g);
+                            const float psi = psi_value(psi_bits(tau, N));
+                            const float w = weight(g, N, (float)b, psi, fabs(p - pc) >= zone, radon_first_sample(tau, N), n_s);
                             if (k < first || k >= first + NL) CHECK(w < 1e-6f);
                             else acc[i * NL + k - first] += (double)w * val;
                         }
@@ -115,7 +138,7 @@ int main() {
     const struct { int W, H, n_alpha, n_t; double ds; } cases[] = {
         {64, 64, 24, 65, 0.5},  {128, 96, 19, 107, 0.5}, {2, 2, 8, 5, 1.0},    {97, 61, 16, 75, 0.7},
         {61, 130, 12, 300, 0.5}, {150, 3, 16, 99, 0.5},  {3, 150, 17, 99, 0.31}, {70, 70, 9, 1001, 1.0},
-        {80, 60, 12, 40, 0.13}, {200, 150, 13, 43, 0.5},
+        {80, 60, 12, 40, 0.13}, {200, 150, 13, 43, 0.5}, {64, 90, 21, 80, 0.6}, {64, 90, 20, 80, 0.95},
     };
     for (auto &t : cases)
         if (run(t.W, t.H, t.n_alpha, t.n_t, t.ds, worst)) return 1;

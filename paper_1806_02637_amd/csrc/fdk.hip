@@ -345,10 +345,11 @@ __global__ __launch_bounds__(256) void fdk_border_kernel(int n_views, int W, int
 constexpr int kBpTile = 16;  // voxel columns per workgroup side
 constexpr int kBpSlab = 16;  // slices per thread
 // LDS window of one view: up to ROWS cell rows x kBpCols elements, each the
-// value and its difference to the next row.  Rows are kBpPitch elements apart,
-// so that the rows of a gather start on different LDS banks.
+// value and its difference to the next row.  Rows are kBpPitch elements apart:
+// 16 LDS banks, so that the two to four rows that a gather's lanes meet do not
+// share banks (512^3, 31.2 ms at 66, 29.1 at 72, 32.5 at 80).
 constexpr int kBpCols = 64;
-constexpr int kBpPitch = 66;
+constexpr int kBpPitch = 72;
 constexpr int kBpWinChunk = 64;  // views whose windows are computed together
 
 // Cell of a padded-view coordinate x: returns the fraction x - floor(x) and
@@ -416,14 +417,17 @@ __device__ __forceinline__ int4 bp_window(const FdkView &w, float xb, float yb, 
 // row's value and the difference to the next row, so that an update is four
 // multiply-adds on the cell's two elements.
 //
-// 512^3 voxels of 0.4 mm from 496 views of 1240 x 960: 31.2 ms; 38.3 ms with
+// 512^3 voxels of 0.4 mm from 496 views of 1240 x 960: 26.5 ms; 38.3 ms with
 // row pairs kept in memory (twice the bytes to stage) and a bilinear step of
-// seven operations on cells clamped one by one.  13 instructions per update,
-// 5 of them a view's constants and staging; issue 68 % busy, LDS 73 % (11.6
-// cycles a gather, 3.6 of them bank conflicts), texture data path 68 %.  Taller
-// tiles spread the constants over 24 or 32 slices but leave fewer waves: 33.0
-// and 33.2 ms.  248 views of 620 x 480, 256^3 at 0.8 mm, all six motion
-// parameters: 2.77 against 3.31 ms.
+// seven operations on cells clamped one by one, 31.2 ms with lanes row by row
+// over the 8 x 8 columns and rows 66 elements apart (3.6 of a gather's 11.6
+// cycles bank conflicts, 0.6 now).  13.4 instructions per update, 5.4 of them a
+// view's constants and staging: the issue slots are 91 % full.  Taller
+// tiles spread the constants over 24 or 32 slices but leave fewer waves (33.0
+// and 33.2 ms against 31.2); two windows and one barrier a view leave three
+// workgroups to a CU (36.9); gathers issued four slices ahead gain nothing
+// (32.2).  248 views of 620 x 480, 256^3 at 0.8 mm, all six motion
+// parameters: 2.76 against 3.31 ms.
 template <int ROWS>
 __global__ __launch_bounds__(256, 4) void fdk_backproject_kernel(const float *__restrict__ Qp,
                                                                  const FdkView *__restrict__ views, int n_all, int W,
@@ -441,11 +445,12 @@ __global__ __launch_bounds__(256, 4) void fdk_backproject_kernel(const float *__
     views += v_first;
     Qp += (int64_t)v_first * (H + 4) * (W + 4);
     const int tx = tile % tiles_x, ty = (tile / tiles_x) % tiles_y, tz = tile / (tiles_x * tiles_y);
-    // each wave takes an 8 x 8 quarter of the 16 x 16 tile: its 64 voxel
-    // columns project onto a compact detector patch
+    // each wave takes an 8 x 8 quarter of the 16 x 16 tile, and each 16 lanes
+    // of it 4 x 4 voxel columns: the lanes that LDS serves together project
+    // onto a compact patch, whose cells share elements instead of banks
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int ix = tx * kBpTile + (wave & 1) * 8 + (lane & 7);
-    const int iy = ty * kBpTile + (wave >> 1) * 8 + (lane >> 3);
+    const int ix = tx * kBpTile + (wave & 1) * 8 + (lane & 3) + (lane >> 4 & 1) * 4;
+    const int iy = ty * kBpTile + (wave >> 1) * 8 + (lane >> 2 & 3) + (lane >> 5) * 4;
     const int iz0 = tz * kBpSlab;
     const float s = vol.voxel_mm;
     const float hx = 0.5f * (float)(vol.nx - 1), hy = 0.5f * (float)(vol.ny - 1), hz = 0.5f * (float)(vol.nz - 1);
@@ -655,7 +660,7 @@ hipError_t launch_fdk(const float *images, const ViewGeom *nominal, const ViewGe
     // the source, a cell of margin on each side and the rounding to cells
     const float r = 0.5f * vol.voxel_mm * hypotf((float)vol.nx, (float)vol.ny);
     const float rows = r < source_mm ? px_per_voxel * 15.0f * source_mm / (source_mm - r) + 4.0f : 1e9f;
-    // (512^3 at 0.4 mm fits 44 rows: 31.2 ms, 32.3 with 56)
+    // (512^3 at 0.4 mm fits 44 rows; 56 cost 3 % there)
     if (rows <= 44.0f)
         return launch_backproject<44>(Qp, views, n_views, W, H, vol, parts, parts_floats, out, s);
     return launch_backproject<56>(Qp, views, n_views, W, H, vol, parts, parts_floats, out, s);

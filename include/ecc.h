@@ -112,7 +112,9 @@ ecc_status ecc_scan_set_sinograms(ecc_ctx *ctx, int32_t scan_id, int32_t n_alpha
                                   const float *sino, int32_t sino_on_device, int32_t dtype);
 
 /* Copies one view's resident sinogram back, decoded to FP32, as
- * [n_alpha + 1][n_t] into host memory `out` (synchronous). */
+ * [n_alpha + 1][n_t] into host memory `out` (synchronous).  Staged through 4 MiB
+ * of pinned host memory that the context makes on the first call and gives
+ * back in ecc_destroy. */
 ecc_status ecc_scan_read_sinogram(ecc_ctx *ctx, int32_t scan_id, int32_t view, float *out);
 
 /* Releases a scan and its device memory (after the device is idle). */
